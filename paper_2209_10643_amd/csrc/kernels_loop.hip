@@ -548,8 +548,9 @@ __device__ __forceinline__ void jacobi_strip(const float *sp, float *dp, int ld,
 // NT: the grids exceed the last-level cache, so the new grid is stored with
 // the non-temporal hint (a grid that fits is read back from that cache by the
 // next sweep and is stored normally).
-template <int TH, int RED, bool NT>
+template <int RED, bool NT>
 __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP p, RedK R) {
+  const int TH = S.tile[0];
   const int lane = threadIdx.x % WAVE;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), NW = blockDim.x / WAVE;
   // The launch's cross-workgroup work goes to one extra workgroup, launched
@@ -615,35 +616,22 @@ bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S) {
   return true;
 }
 
-template <int TH, bool NT>
-static hipError_t go_jacobi_nt(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
+template <bool NT>
+static hipError_t go_jacobi(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
   const dim3 g(S.T + (jacobi_extra_wg(R) ? 1 : 0)), b(S.U);
   switch (R.op) {
-    case RED_NONE: hipLaunchKernelGGL((k_jacobi_tile<TH, RED_NONE, NT>), g, b, 0, st, L, S, p, R); break;
-    case RED_SUM: hipLaunchKernelGGL((k_jacobi_tile<TH, RED_SUM, NT>), g, b, 0, st, L, S, p, R); break;
-    case RED_MAX: hipLaunchKernelGGL((k_jacobi_tile<TH, RED_MAX, NT>), g, b, 0, st, L, S, p, R); break;
-    default: hipLaunchKernelGGL((k_jacobi_tile<TH, RED_MIN, NT>), g, b, 0, st, L, S, p, R); break;
+    case RED_NONE: hipLaunchKernelGGL((k_jacobi_tile<RED_NONE, NT>), g, b, 0, st, L, S, p, R); break;
+    case RED_SUM: hipLaunchKernelGGL((k_jacobi_tile<RED_SUM, NT>), g, b, 0, st, L, S, p, R); break;
+    case RED_MAX: hipLaunchKernelGGL((k_jacobi_tile<RED_MAX, NT>), g, b, 0, st, L, S, p, R); break;
+    default: hipLaunchKernelGGL((k_jacobi_tile<RED_MIN, NT>), g, b, 0, st, L, S, p, R); break;
   }
   return hipGetLastError();
 }
 
-template <int TH>
-static hipError_t go_jacobi(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
+hipError_t launch_jacobi_tile(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
   // source and destination rows the sweep touches, against the 256 MB cache
   const uint64_t bytes = 2ull * (uint64_t)(L.cnt[0] + 2) * (uint64_t)p.ld * 4u;
-  return bytes > (256ull << 20) ? go_jacobi_nt<TH, true>(p, L, S, R, st) : go_jacobi_nt<TH, false>(p, L, S, R, st);
-}
-
-hipError_t launch_jacobi_tile(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
-  switch (S.tile[0]) {
-    case 4: return go_jacobi<4>(p, L, S, R, st);
-    case 8: return go_jacobi<8>(p, L, S, R, st);
-    case 16: return go_jacobi<16>(p, L, S, R, st);
-    case 32: return go_jacobi<32>(p, L, S, R, st);
-    case 64: return go_jacobi<64>(p, L, S, R, st);
-    case 128: return go_jacobi<128>(p, L, S, R, st);
-  }
-  return hipErrorInvalidValue;
+  return bytes > (256ull << 20) ? go_jacobi<true>(p, L, S, R, st) : go_jacobi<false>(p, L, S, R, st);
 }
 
 // ----------------------------------------- 7 x 7 filter, wavefront strips
@@ -744,8 +732,8 @@ __device__ __forceinline__ void f7_strip(const Filter7P &p, const float (&wk)[49
   }
 }
 
-template <int TH>
 __global__ void __launch_bounds__(1024) k_filter7_tile(LoopK L, SchedK S, Filter7P p, RedK R) {
+  const int TH = S.tile[0];
   const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE, NW = blockDim.x / WAVE;
   const int team = xcd_team(blockIdx.x, gridDim.x);
   const int SH = (TH + NW - 1) / NW;
@@ -795,15 +783,7 @@ bool filter7_tile_supports(const Filter7P &p, const LoopK &L, const SchedK &S) {
 }
 
 hipError_t launch_filter7_tile(const Filter7P &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
-  const dim3 g(S.T), b(S.U);
-  switch (S.tile[0]) {
-    case 4: hipLaunchKernelGGL(k_filter7_tile<4>, g, b, 0, st, L, S, p, R); break;
-    case 8: hipLaunchKernelGGL(k_filter7_tile<8>, g, b, 0, st, L, S, p, R); break;
-    case 16: hipLaunchKernelGGL(k_filter7_tile<16>, g, b, 0, st, L, S, p, R); break;
-    case 32: hipLaunchKernelGGL(k_filter7_tile<32>, g, b, 0, st, L, S, p, R); break;
-    case 64: hipLaunchKernelGGL(k_filter7_tile<64>, g, b, 0, st, L, S, p, R); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL(k_filter7_tile, dim3(S.T), dim3(S.U), 0, st, L, S, p, R);
   return hipGetLastError();
 }
 
