@@ -39,6 +39,11 @@ hipError_t launch_generic(int32_t body, const void *payload, const LoopK &L, con
                           const RedK &R, hipStream_t st);
 hipError_t launch_stream4(int32_t body, const void *payload, const LoopK &L, const SchedK &S,
                           const RedK &R, hipStream_t st);
+// AXPY and SUM under schedules whose units own runs of consecutive iterations.
+hipError_t launch_team_stream(int32_t body, const void *payload, const LoopK &L, const SchedK &S,
+                              const RedK &R, hipStream_t st);
+bool team_stream_body(int32_t body, int32_t sum_dtype, int32_t op);
+bool team_stream_supports(int32_t body, const void *payload, const LoopK &L, const SchedK &S, const RedK &R);
 hipError_t launch_fold(const FoldK &F, hipStream_t st);
 hipError_t launch_jacobi_tile(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R,
                               hipStream_t st);
