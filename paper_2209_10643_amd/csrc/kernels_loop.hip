@@ -214,6 +214,14 @@ hipError_t launch_generic(int32_t body, const void *payload, const LoopK &L, con
     }
     case 3: return go_generic(BJacobi{*(const JacobiP *)payload}, L, S, R, st);
     case 4:
+      if (mm_f32_supports(*(const MatmulP *)payload, L, S)) {
+        if (R.fold.count > 0) {  // these tiles take no fold along
+          const hipError_t e = launch_fold(R.fold, st);
+          if (e != hipSuccess) return e;
+        }
+        return launch_mm_f32(*(const MatmulP *)payload, S, st);
+      }
+      [[fallthrough]];
     case 5:
     case 6: return go_generic(BMatmul{*(const MatmulP *)payload}, L, S, R, st);
     case 8: return go_generic(BOwner{*(const OwnerP *)payload, S.U}, L, S, R, st);

@@ -6,8 +6,8 @@
 // (not in the paper): float32; A, B rounded to bfloat16 (round to nearest
 // even) with float32 accumulation; and the three-pass split
 // A_lo B_hi + A_hi B_lo + A_hi B_hi that recovers float32 accuracy.
+#include "matmul_tiles.h"
 #include "upir.h"
-#include "upir_launch.h"
 
 namespace upir {
 
@@ -179,29 +179,6 @@ hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st) {
 // for the wide tile). The split variant accumulates lo_A hi_B, hi_A lo_B and
 // hi_A hi_B into one float32 sum. float32 uses v_mfma_f32_32x32x2f32 over A
 // (M x K) and B (K x N) directly.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
-template <int BM, int BN, int WM, int WN>
-__device__ inline void store_c(const MatmulP &p, int64_t row0, int64_t col0, const f32x16 (&acc)[BM / WM / 32][BN / WN / 32]) {
-  constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int64_t col = col0 + wn * (BN / WN) + j * 32 + (lane & 31);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int64_t row = row0 + wm * (BM / WM) + i * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
-        if (row < p.M && col < p.N) p.C[row * p.ldc + col] = acc[i][j][r];
-      }
-    }
-}
-
 // The same stores with the non-temporal hint (C is written once and not read
 // again here); the row and column tests are hoisted out of the element loop,
 // and left out for tiles known to be whole (CHECK false: each test became a
@@ -236,21 +213,6 @@ __device__ inline void store_c_nt(const MatmulP &p, int64_t row0, int64_t col0, 
 // do the eight rows of an 8-lane phase (2 rows per 128 bytes); a phase that
 // writes four whole rows covers the banks once whatever the swizzle.
 __device__ inline int mmw_swz(int r) { return ((r >> 2) & 1) | ((((r >> 1) ^ (r >> 3)) & 1) << 1); }
-
-// Tiles owned by this team under the tiled schedule.
-template <class F>
-__device__ inline void for_team_tiles(const SchedK &S, F &&f) {
-  const int team = xcd_team(blockIdx.x, gridDim.x);
-  if (S.policy == POL_STATIC) {
-    int64_t lo, hi;
-    block_range(S.ntiles, S.T, team, lo, hi);
-    for (int64_t m = lo; m < hi; ++m) f(m);
-  } else {
-    const int64_t c = S.chunk;
-    for (int64_t m0 = (int64_t)team * c; m0 < S.ntiles; m0 += (int64_t)S.T * c)
-      for (int64_t m = m0; m < m0 + c && m < S.ntiles; ++m) f(m);
-  }
-}
 
 template <int NPROD, int BM, int BN, int WM, int WN, int BK, int STAGES>
 __global__ void __launch_bounds__(WM * WN * 64) k_mm_bf16(MatmulP p, SchedK S) {
@@ -600,95 +562,6 @@ __global__ void __launch_bounds__(256) k_mm_bf16_wide(MatmulP p, SchedK S) {
   });
 }
 
-template <int BM, int BN, int WM, int WN, int BK>
-__global__ void __launch_bounds__(WM * WN * 64) k_mm_f32(MatmulP p, SchedK S) {
-  constexpr int NTH = WM * WN * 64;
-  constexpr int PA = BK + 4;   // floats per A row in LDS
-  constexpr int PB = BN + 8;   // floats per B row (k) in LDS
-  constexpr int FM = BM / WM / 32, FN = BN / WN / 32;
-  constexpr int CA = BM * (BK / 4) / NTH, CB = BK * (BN / 4) / NTH;
-  static_assert(BM * (BK / 4) % NTH == 0 && BK * (BN / 4) % NTH == 0, "chunk split");
-  constexpr int STAGEF = BM * PA + BK * PB;  // floats per LDS stage (two stages)
-  extern __shared__ __attribute__((aligned(16))) float ldsf[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int64_t K = p.K;
-
-  for_team_tiles(S, [&](int64_t m) {
-    const int64_t row0 = (S.t0[0] + m / S.nt[1]) * BM, col0 = (S.t0[1] + m % S.nt[1]) * BN;
-    f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{};
-    f32x4v ra[CA], rb[CB];
-    auto fetch = [&](int64_t k0) {
-#pragma unroll
-      for (int q = 0; q < CA; ++q) {
-        const int c = tid + q * NTH, r = c / (BK / 4), kc = c % (BK / 4);
-        const int64_t gr = row0 + r, gk = k0 + kc * 4;
-        ra[q] = (gr < p.M && gk < K) ? *(const f32x4v *)(p.A + gr * p.lda + gk) : f32x4v{};
-      }
-#pragma unroll
-      for (int q = 0; q < CB; ++q) {
-        const int c = tid + q * NTH, r = c / (BN / 4), nc = c % (BN / 4);
-        const int64_t gk = k0 + r, gc = col0 + nc * 4;
-        rb[q] = (gk < K && gc < p.N) ? *(const f32x4v *)(p.B + gk * p.ldb + gc) : f32x4v{};
-      }
-    };
-    auto stage = [&](int buf) {
-      float *sA = ldsf + buf * STAGEF, *sB = sA + BM * PA;
-#pragma unroll
-      for (int q = 0; q < CA; ++q) {
-        const int c = tid + q * NTH, r = c / (BK / 4), kc = c % (BK / 4);
-        *(f32x4v *)(sA + r * PA + kc * 4) = ra[q];
-      }
-#pragma unroll
-      for (int q = 0; q < CB; ++q) {
-        const int c = tid + q * NTH, r = c / (BN / 4), nc = c % (BN / 4);
-        *(f32x4v *)(sB + r * PB + nc * 4) = rb[q];
-      }
-    };
-    __syncthreads();  // the previous tile's readers are done with both stages
-    fetch(0);
-    stage(0);
-    __syncthreads();
-    const int g = lane >> 5;
-    int cur = 0;
-    for (int64_t k0 = 0; k0 < K; k0 += BK) {
-      const bool more = k0 + BK < K;
-      if (more) fetch(k0 + BK);
-      const float *sA = ldsf + cur * STAGEF, *sB = sA + BM * PA;
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 8) {
-        // group g takes k = kk + 4g + s at MFMA step s (same for A and B)
-        f32x4v a[FM];
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-          a[i] = *(const f32x4v *)(sA + (wm * (BM / WM) + i * 32 + (lane & 31)) * PA + kk + 4 * g);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          float b[FN];
-#pragma unroll
-          for (int j = 0; j < FN; ++j) b[j] = sB[(kk + 4 * g + s) * PB + wn * (BN / WN) + j * 32 + (lane & 31)];
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j)
-              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][s], b[j], acc[i][j], 0, 0, 0);
-        }
-      }
-      // the next step goes into the other stage; one barrier then both makes
-      // it visible and keeps this stage from being overwritten (two steps on)
-      // before every wave has read it
-      if (more) stage(cur ^ 1);
-      __syncthreads();
-      cur ^= 1;
-    }
-    store_c<BM, BN, WM, WN>(p, row0, col0, acc);
-  });
-}
-
 // Kernel configurations: (kind, tile) -> block size.
 struct MMConf { int kind, bm, bn, threads; };
 static const MMConf kMM[] = {
@@ -696,6 +569,7 @@ static const MMConf kMM[] = {
     {UPIR_BODY_MATMUL_BF16, 256, 256, 512}, {UPIR_BODY_MATMUL_BF16, 128, 128, 256},
     {UPIR_BODY_MATMUL_SPLIT3, 256, 256, 512}, {UPIR_BODY_MATMUL_SPLIT3, 128, 128, 256},
     {UPIR_BODY_MATMUL_F32, 128, 128, 256}, {UPIR_BODY_MATMUL_F32, 256, 128, 512},
+    {UPIR_BODY_MATMUL_F32, 64, 64, 512}, {UPIR_BODY_MATMUL_F32, 32, 32, 512},
 };
 
 bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
@@ -720,18 +594,6 @@ bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
   return true;
 }
 
-template <class Kern>
-static hipError_t go_mm(Kern k, const MatmulP &p, const SchedK &S, size_t lds, hipStream_t st) {
-  static bool attr_set = false;  // raise the dynamic LDS limit once per kernel
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  hipLaunchKernelGGL(k, dim3(S.T), dim3(S.U), lds, st, p, S);
-  return hipGetLastError();
-}
-
 hipError_t launch_matmul_mfma(const MatmulP &p, const LoopK &, const SchedK &S, hipStream_t st) {
   const int bm = S.tile[0], bn = S.tile[1];
   // LDS bytes = stages x (BM + BN) rows x pitch x 2 bytes (x 2 for the lo halves)
@@ -741,24 +603,22 @@ hipError_t launch_matmul_mfma(const MatmulP &p, const LoopK &, const SchedK &S, 
     const size_t lds = MMW_STAGES * MMW_STAGE;
     const bool even = (p.K + MMW_BK - 1) / MMW_BK % 2 == 0;  // NSEG x steps is even iff steps is
     if (p.kind == UPIR_BODY_MATMUL_BF16) {
-      if (al) return even ? go_mm(k_mm_bf16_wide<1, true, true>, p, S, lds, st) : go_mm(k_mm_bf16_wide<1, true, false>, p, S, lds, st);
-      return even ? go_mm(k_mm_bf16_wide<1, false, true>, p, S, lds, st) : go_mm(k_mm_bf16_wide<1, false, false>, p, S, lds, st);
+      if (al) return even ? go_mm<k_mm_bf16_wide<1, true, true>>(p, S, lds, st) : go_mm<k_mm_bf16_wide<1, true, false>>(p, S, lds, st);
+      return even ? go_mm<k_mm_bf16_wide<1, false, true>>(p, S, lds, st) : go_mm<k_mm_bf16_wide<1, false, false>>(p, S, lds, st);
     }
-    if (al) return even ? go_mm(k_mm_bf16_wide<3, true, true>, p, S, lds, st) : go_mm(k_mm_bf16_wide<3, true, false>, p, S, lds, st);
-    return even ? go_mm(k_mm_bf16_wide<3, false, true>, p, S, lds, st) : go_mm(k_mm_bf16_wide<3, false, false>, p, S, lds, st);
+    if (al) return even ? go_mm<k_mm_bf16_wide<3, true, true>>(p, S, lds, st) : go_mm<k_mm_bf16_wide<3, true, false>>(p, S, lds, st);
+    return even ? go_mm<k_mm_bf16_wide<3, false, true>>(p, S, lds, st) : go_mm<k_mm_bf16_wide<3, false, false>>(p, S, lds, st);
   }
   if (p.kind == UPIR_BODY_MATMUL_BF16) {
-    if (bm == 256) return go_mm(k_mm_bf16<1, 256, 256, 2, 4, 64, 2>, p, S, 2 * (256 + 256) * 72 * 2, st);
-    return go_mm(k_mm_bf16<1, 128, 128, 2, 2, 64, 2>, p, S, 2 * (128 + 128) * 72 * 2, st);
+    if (bm == 256) return go_mm<k_mm_bf16<1, 256, 256, 2, 4, 64, 2>>(p, S, 2 * (256 + 256) * 72 * 2, st);
+    return go_mm<k_mm_bf16<1, 128, 128, 2, 2, 64, 2>>(p, S, 2 * (128 + 128) * 72 * 2, st);
   }
   if (p.kind == UPIR_BODY_MATMUL_SPLIT3) {
     // two stages of (A_hi, B_hi, A_lo, B_lo) x rows x 64 bytes (swizzled, unpadded)
-    if (bm == 256) return go_mm(k_mm_bf16<3, 256, 256, 2, 4, 32, 2>, p, S, 2 * 2 * (256 + 256) * 32 * 2, st);
-    return go_mm(k_mm_bf16<3, 128, 128, 2, 2, 32, 2>, p, S, 2 * 2 * (128 + 128) * 32 * 2, st);
+    if (bm == 256) return go_mm<k_mm_bf16<3, 256, 256, 2, 4, 32, 2>>(p, S, 2 * 2 * (256 + 256) * 32 * 2, st);
+    return go_mm<k_mm_bf16<3, 128, 128, 2, 2, 32, 2>>(p, S, 2 * 2 * (128 + 128) * 32 * 2, st);
   }
-  // two LDS stages of (BM x (BK + 4) + BK x (BN + 8)) floats
-  if (bm == 256 && bn == 128) return go_mm(k_mm_f32<256, 128, 4, 2, 32>, p, S, 2 * (256 * 36 + 32 * 136) * 4, st);
-  return go_mm(k_mm_f32<128, 128, 2, 2, 32>, p, S, 2 * (128 * 36 + 32 * 136) * 4, st);
+  return launch_mm_f32(p, S, st);
 }
 
 }  // namespace upir

@@ -621,6 +621,8 @@ static std::vector<Cand> candidates(upir_ctx *c, const upir_loop_obj *lp) {
     case UPIR_BODY_MATMUL_F32:
       add(0, 256, UPIR_SCHED_STATIC, 0, 128, 128);
       add(0, 512, UPIR_SCHED_STATIC, 0, 256, 128);
+      add(0, 512, UPIR_SCHED_STATIC, 0, 64, 64);
+      add(0, 512, UPIR_SCHED_STATIC, 0, 32, 32);
       break;
     case UPIR_BODY_MATMUL_BF16:
     case UPIR_BODY_MATMUL_SPLIT3:

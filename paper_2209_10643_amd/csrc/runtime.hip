@@ -719,16 +719,28 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // 4096^3); 128 x 128 tiles when C has fewer 256 x 256 tiles than half
       // the device's CUs (measured with 256 CUs: 128 x 128 faster at 2048^2,
       // 64 large tiles; 256 x 256 faster at 3072^2, 144 large tiles).
-      // float32: 256 x 128 on 8 wavefronts when C has at least one such tile
-      // per CU (1.08 against 1.11 ms at 4096^3), else 128 x 128 on 4.
+      // float32: the tile with the smallest estimate of (tiles per CU, rounded
+      // up) x (time of a tile per k, measured with every CU busy): 126 ns for
+      // 256 x 128 on 8 wavefronts, 70 for 128 x 128 on 4, 22 for 64 x 64 and
+      // 7.3 for 32 x 32 on 8 that share the k range (1024^3: 25 us on 64 x 64
+      // against 77 on 128 x 128; 512^3: 7 us on 32 x 32 against 14; 2000^3:
+      // 155 us on 128 x 128 against 186 on 64 x 64).
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = 0;
       sp.num_units = 256;
       if (lp->kind == UPIR_BODY_MATMUL_F32) {
-        const bool big = cdiv(lp->cnt[0], 256) * cdiv(lp->cnt[1], 128) >= c->num_cus;
-        sc.tile[0] = big ? 256 : 128;
-        sc.tile[1] = 128;
-        sp.num_units = big ? 512 : 256;
+        static const struct { int bm, bn, units; double ns; } tiles[] = {
+            {256, 128, 512, 126.0}, {128, 128, 256, 70.0}, {64, 64, 512, 22.0}, {32, 32, 512, 7.3}};
+        double best = 0.0;
+        for (const auto &t : tiles) {
+          const double cost = (double)cdiv(cdiv(lp->cnt[0], t.bm) * cdiv(lp->cnt[1], t.bn), c->num_cus) * t.ns;
+          if (sc.tile[0] == 0 || cost < best) {
+            best = cost;
+            sc.tile[0] = t.bm;
+            sc.tile[1] = t.bn;
+            sp.num_units = t.units;
+          }
+        }
         break;
       }
       const bool small = 2 * cdiv(lp->cnt[0], 256) * cdiv(lp->cnt[1], 256) < c->num_cus;

@@ -54,6 +54,9 @@ hipError_t launch_matvec_wave(const MatvecP &p, const LoopK &L, const SchedK &S,
 // MFMA matmul over tiles of C (tile[0] x tile[1]); S gives the team schedule over tiles.
 hipError_t launch_matmul_mfma(const MatmulP &p, const LoopK &L, const SchedK &S, hipStream_t st);
 bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S);
+// float32 tiles for operands the above leaves out (any pitch and alignment); the schedule decides.
+bool mm_f32_supports(const MatmulP &p, const LoopK &L, const SchedK &S);
+hipError_t launch_mm_f32(const MatmulP &p, const SchedK &S, hipStream_t st);
 // BF16 pre-pass: A (M x K) -> ah, al; B (K x N) -> bh, bl transposed (N x K).
 hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st);
 // The 256 x 256 four-wavefront bfloat16 tile (it reads the k-panel workspace layout).
