@@ -66,16 +66,17 @@ struct BMatmul {
   MatmulP p;
   __device__ void operator()(int64_t, const int64_t *iv, int, int, Acc &, int) const {
     const int64_t i = iv[0], j = iv[1];
+    const int64_t kp = mm_kpad(p.K);  // workspace rows
     float acc = 0.0f;
     if (p.kind == 4) {
       for (int64_t k = 0; k < p.K; ++k) acc = __builtin_fmaf(p.A[i * p.lda + k], p.B[k * p.ldb + j], acc);
     } else if (p.kind == 5) {
       for (int64_t k = 0; k < p.K; ++k)
-        acc = __builtin_fmaf(bf16_to_f32(p.ah[i * p.K + k]), bf16_to_f32(p.bh[j * p.K + k]), acc);
+        acc = __builtin_fmaf(bf16_to_f32(p.ah[i * kp + k]), bf16_to_f32(p.bh[j * kp + k]), acc);
     } else {
       for (int64_t k = 0; k < p.K; ++k) {
-        const float ah = bf16_to_f32(p.ah[i * p.K + k]), al = bf16_to_f32(p.al[i * p.K + k]);
-        const float bh = bf16_to_f32(p.bh[j * p.K + k]), bl = bf16_to_f32(p.bl[j * p.K + k]);
+        const float ah = bf16_to_f32(p.ah[i * kp + k]), al = bf16_to_f32(p.al[i * kp + k]);
+        const float bh = bf16_to_f32(p.bh[j * kp + k]), bl = bf16_to_f32(p.bl[j * kp + k]);
         acc = __builtin_fmaf(al, bh, acc);
         acc = __builtin_fmaf(ah, bl, acc);
         acc = __builtin_fmaf(ah, bh, acc);

@@ -18,30 +18,33 @@ __device__ inline uint16_t to_bf16_rne(float x) {
 __device__ inline float bf16f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // Workspace element (row, k) of an operand with `rows` rows: rows of K
-// (layout 0), or k-panels of 32 (layout 1): panel k / 32 holds 32 k of every
-// row, row after row, so the rows x 32 block one k step reads is contiguous.
+// rounded up to 32 (layout 0), or k-panels of 32 (layout 1): panel k / 32
+// holds 32 k of every row, row after row, so the rows x 32 block one k step
+// reads is contiguous. In both, the chunk of eight k that holds k = K - 1 is
+// filled up with zeros, so the tiles read whole chunks for any K.
 __device__ inline int64_t ws_index(int panel, int64_t row, int64_t k, int64_t rows, int64_t K) {
-  return panel ? (((k >> 5) * rows + row) << 5) + (k & 31) : row * K + k;
+  return panel ? (((k >> 5) * rows + row) << 5) + (k & 31) : row * mm_kpad(K) + k;
 }
 
-// A (M x K, lda) -> ah / al (M x K, dense). Row-major, coalesced.
+// Element forms (workspace off a 16-byte boundary): every k up to the end of
+// the last chunk of eight. A (M x K, lda) -> ah / al, row-major, coalesced.
 __global__ void __launch_bounds__(256) k_split_rows(const float *__restrict__ A, int64_t M, int64_t K, int64_t lda,
                                                     uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int panel) {
-  const int64_t total = M * K;
+  const int64_t KE = (K + 7) / 8 * 8, total = M * KE;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = e / K, k = e - i * K, d = ws_index(panel, i, k, M, K);
-    const float x = A[i * lda + k];
+    const int64_t i = e / KE, k = e - i * KE, d = ws_index(panel, i, k, M, K);
+    const float x = k < K ? A[i * lda + k] : 0.0f;
     const uint16_t h = to_bf16_rne(x);
     hi[d] = h;
     if (lo) lo[d] = to_bf16_rne(x - bf16f(h));
   }
 }
 
-// B (K x N, ldb) -> bh / bl transposed (N x K, dense) through a 64 x 64 LDS tile.
+// B (K x N, ldb) -> bh / bl transposed (N x K) through a 64 x 64 LDS tile.
 __global__ void __launch_bounds__(256) k_split_cols(const float *__restrict__ B, int64_t K, int64_t N, int64_t ldb,
                                                     uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int panel) {
   __shared__ float t[64][65];
-  const int64_t k0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
+  const int64_t k0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64, KE = (K + 7) / 8 * 8;
   const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;  // 64 x 4
   for (int r = ty; r < 64; r += 4) {
     const int64_t k = k0 + r, n = n0 + tx;
@@ -50,7 +53,7 @@ __global__ void __launch_bounds__(256) k_split_cols(const float *__restrict__ B,
   __syncthreads();
   for (int r = ty; r < 64; r += 4) {
     const int64_t n = n0 + r, k = k0 + tx;
-    if (n < N && k < K) {
+    if (n < N && k < KE) {
       const float x = t[tx][r];
       const uint16_t h = to_bf16_rne(x);
       const int64_t d = ws_index(panel, n, k, N, K);
@@ -60,20 +63,30 @@ __global__ void __launch_bounds__(256) k_split_cols(const float *__restrict__ B,
   }
 }
 
-// Vector forms (K % 8 == 0, 16-byte aligned rows): eight consecutive k per
-// thread, two 16-byte loads and one 16-byte store of eight bfloat16 per
-// output array.
-typedef float f32x4s __attribute__((ext_vector_type(4)));
+// Vector forms: eight consecutive k per thread, two 16-byte loads (at any
+// alignment) and one 16-byte store of eight bfloat16 per output array.
+typedef float f32x4s __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned u32x4s __attribute__((ext_vector_type(4)));
 __device__ inline unsigned pack2(uint16_t a, uint16_t b) { return (unsigned)a | ((unsigned)b << 16); }
 
 __global__ void __launch_bounds__(256) k_split_rows8(const float *__restrict__ A, int64_t M, int64_t K, int64_t lda,
                                                      uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int panel) {
-  const int64_t chunks = M * (K / 8);
+  const int64_t KC = (K + 7) / 8, chunks = M * KC;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < chunks; c += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t e = 8 * c, i = e / K, k = e - i * K;
-    const f32x4s v0 = *(const f32x4s *)(A + i * lda + k), v1 = *(const f32x4s *)(A + i * lda + k + 4);
-    const float x[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+    const int64_t i = c / KC, k = 8 * (c - i * KC);
+    const float *a = A + i * lda + k;
+    float x[8];
+    if (k + 8 <= K) {
+      const f32x4s v0 = *(const f32x4s *)a, v1 = *(const f32x4s *)(a + 4);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        x[q] = v0[q];
+        x[4 + q] = v1[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) x[q] = k + q < K ? a[q] : 0.0f;
+    }
     uint16_t h[8], l[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -112,7 +125,7 @@ __global__ void __launch_bounds__(256) k_split_cols8(const float *__restrict__ B
   for (int q = threadIdx.x; q < 64 * 8; q += 256) {  // 64 output rows x 8 chunks of 8 k
     const int r = q / 8, kc = 8 * (q % 8);
     const int64_t n = n0 + r, k = k0 + kc;
-    if (n >= N || k >= K) continue;  // K % 8 == 0: a chunk is all in or all out
+    if (n >= N || k >= K) continue;  // the tile holds zeros past K
     uint16_t h[8], l[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -127,20 +140,17 @@ __global__ void __launch_bounds__(256) k_split_cols8(const float *__restrict__ B
 }
 
 hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st) {
-  // vector forms: K % 8 == 0, 16-byte aligned operands and rows, aligned workspace
-  const bool ws_ok = (uintptr_t)p.ah % 16 == 0 && (uintptr_t)p.bh % 16 == 0 &&
-                     (!need_lo || ((uintptr_t)p.al % 16 == 0 && (uintptr_t)p.bl % 16 == 0));
-  const bool vec = p.K % 8 == 0 && ws_ok;
-  const bool vec_a = vec && p.lda % 4 == 0 && (uintptr_t)p.A % 16 == 0;
-  const bool vec_b = vec && p.ldb % 4 == 0 && (uintptr_t)p.B % 16 == 0;
+  // vector forms: 16-byte aligned workspace arrays
+  const bool vec = (uintptr_t)p.ah % 16 == 0 && (uintptr_t)p.bh % 16 == 0 &&
+                   (!need_lo || ((uintptr_t)p.al % 16 == 0 && (uintptr_t)p.bl % 16 == 0));
   if (p.M > 0 && p.K > 0) {
-    if (vec_a) {
-      const int64_t chunks = p.M * (p.K / 8);
+    if (vec) {
+      const int64_t chunks = p.M * ((p.K + 7) / 8);
       const int g = (int)std::min<int64_t>((chunks + 255) / 256, 16384);
       hipLaunchKernelGGL(k_split_rows8, dim3(g), dim3(256), 0, st, p.A, p.M, p.K, p.lda, p.ah,
                          need_lo ? p.al : nullptr, p.panel);
     } else {
-      const int64_t tot = p.M * p.K;
+      const int64_t tot = p.M * ((p.K + 7) / 8 * 8);
       const int g = (int)std::min<int64_t>((tot + 255) / 256, 8192);
       hipLaunchKernelGGL(k_split_rows, dim3(g), dim3(256), 0, st, p.A, p.M, p.K, p.lda, p.ah,
                          need_lo ? p.al : nullptr, p.panel);
@@ -148,7 +158,7 @@ hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st) {
   }
   if (p.N > 0 && p.K > 0) {
     dim3 g((unsigned)((p.N + 63) / 64), (unsigned)((p.K + 63) / 64));
-    if (vec_b)
+    if (vec)
       hipLaunchKernelGGL(k_split_cols8, g, dim3(256), 0, st, p.B, p.K, p.N, p.ldb, p.bh, need_lo ? p.bl : nullptr,
                          p.panel);
     else
@@ -229,7 +239,7 @@ __global__ void __launch_bounds__(WM * WN * 64) k_mm_bf16(MatmulP p, SchedK S) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int64_t K = p.K;
+  const int64_t K = p.K, KP = mm_kpad(K);
 
   for_team_tiles(S, [&](int64_t m) {
     const int64_t row0 = (S.t0[0] + m / S.nt[1]) * BM, col0 = (S.t0[1] + m % S.nt[1]) * BN;
@@ -245,16 +255,16 @@ __global__ void __launch_bounds__(WM * WN * 64) k_mm_bf16(MatmulP p, SchedK S) {
         const int c = tid + q * NTH, r = c / CPR, kc = c % CPR;
         const int64_t gr = row0 + r, gk = k0 + kc * 8;
         const bool in = gr < p.M && gk < K;
-        ra[q] = in ? *(const u32x4 *)(p.ah + gr * K + gk) : u32x4{};
-        if (NPROD == 3) ral[q] = in ? *(const u32x4 *)(p.al + gr * K + gk) : u32x4{};
+        ra[q] = in ? *(const u32x4 *)(p.ah + gr * KP + gk) : u32x4{};
+        if (NPROD == 3) ral[q] = in ? *(const u32x4 *)(p.al + gr * KP + gk) : u32x4{};
       }
 #pragma unroll
       for (int q = 0; q < CB; ++q) {
         const int c = tid + q * NTH, r = c / CPR, kc = c % CPR;
         const int64_t gc = col0 + r, gk = k0 + kc * 8;
         const bool in = gc < p.N && gk < K;
-        rb[q] = in ? *(const u32x4 *)(p.bh + gc * K + gk) : u32x4{};
-        if (NPROD == 3) rbl[q] = in ? *(const u32x4 *)(p.bl + gc * K + gk) : u32x4{};
+        rb[q] = in ? *(const u32x4 *)(p.bh + gc * KP + gk) : u32x4{};
+        if (NPROD == 3) rbl[q] = in ? *(const u32x4 *)(p.bl + gc * KP + gk) : u32x4{};
       }
     };
     // LDS stage layout: A_hi (BM rows), B_hi (BN rows), then A_lo, B_lo
@@ -570,6 +580,9 @@ static const MMConf kMM[] = {
     {UPIR_BODY_MATMUL_SPLIT3, 256, 256, 512}, {UPIR_BODY_MATMUL_SPLIT3, 128, 128, 256},
     {UPIR_BODY_MATMUL_F32, 128, 128, 256}, {UPIR_BODY_MATMUL_F32, 256, 128, 512},
     {UPIR_BODY_MATMUL_F32, 64, 64, 512}, {UPIR_BODY_MATMUL_F32, 32, 32, 512},
+    {UPIR_BODY_MATMUL_BF16, 128, 128, 512}, {UPIR_BODY_MATMUL_SPLIT3, 128, 128, 512},
+    {UPIR_BODY_MATMUL_BF16, 64, 64, 512}, {UPIR_BODY_MATMUL_SPLIT3, 64, 64, 512},
+    {UPIR_BODY_MATMUL_BF16, 32, 32, 512}, {UPIR_BODY_MATMUL_SPLIT3, 32, 32, 512},
 };
 
 bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
@@ -583,8 +596,7 @@ bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
   if (p.kind == UPIR_BODY_MATMUL_F32) {
     if (p.K % 4 || p.lda % 4 || p.ldb % 4 || p.N % 4) return false;
     if ((uintptr_t)p.A % 16 || (uintptr_t)p.B % 16) return false;
-  } else {
-    if (p.K % 8) return false;
+  } else if (!matmul_direct(p, S)) {
     if ((uintptr_t)p.ah % 16 || (uintptr_t)p.bh % 16) return false;
     if (p.kind == UPIR_BODY_MATMUL_SPLIT3 && ((uintptr_t)p.al % 16 || (uintptr_t)p.bl % 16)) return false;
     // the wide tile addresses each operand with 32-bit buffer offsets
@@ -595,7 +607,8 @@ bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
 }
 
 hipError_t launch_matmul_mfma(const MatmulP &p, const LoopK &, const SchedK &S, hipStream_t st) {
-  const int bm = S.tile[0], bn = S.tile[1];
+  if (matmul_direct(p, S)) return launch_mm_direct(p, S, st);
+  const int bm = S.tile[0];
   // LDS bytes = stages x (BM + BN) rows x pitch x 2 bytes (x 2 for the lo halves)
   if (matmul_wide(p, S)) {
     // whole tiles and whole k-panels: no bounds tests in the load loop

@@ -216,31 +216,8 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) k_mm_f32(MatmulP p, SchedK 
       if (kt < K) fetch_tail(kt, ta, tb);
       __syncthreads();
     }
-    if constexpr (KG == 1) {
-      store_c<BM, BN, WM, WN>(p, row0, col0, acc);
-    } else {
-      // the k groups' sums meet in LDS (every reader of the last stage has
-      // passed the loop's last barrier); each thread adds and stores
-      // elements of C row by row
-      float *red = ldsf;
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = wm * (BM / WM) + i * 32 + 8 * (r / 4) + 4 * g + (r % 4);
-            red[(kg * BM + row) * BN + wn * (BN / WN) + j * 32 + (lane & 31)] = acc[i][j][r];
-          }
-      __syncthreads();
-      for (int e = tid; e < BM * BN; e += NTH) {
-        float s = red[e];
-#pragma unroll
-        for (int h = 1; h < KG; ++h) s += red[h * BM * BN + e];
-        const int64_t row = row0 + e / BN, col = col0 + e % BN;
-        if (row < p.M && col < p.N) p.C[row * p.ldc + col] = s;
-      }
-    }
+    if constexpr (KG == 1) store_c<BM, BN, WM, WN>(p, row0, col0, acc);
+    else store_c_sum<BM, BN, WM, WN, KG>(p, row0, col0, acc, ldsf);
   });
 }
 

@@ -629,6 +629,7 @@ static std::vector<Cand> candidates(upir_ctx *c, const upir_loop_obj *lp) {
       add(0, 256, UPIR_SCHED_STATIC, 0, 128, 128);
       add(0, 256, UPIR_SCHED_STATIC, 0, 256, 256);
       add(0, 512, UPIR_SCHED_STATIC, 0, 256, 256);
+      for (int t : {128, 64, 32}) add(0, 512, UPIR_SCHED_STATIC, 0, t, t);
       break;
     default:
       for (int32_t U : {64, 256}) add(teams(n, U * 4), U, UPIR_SCHED_STATIC, 0);

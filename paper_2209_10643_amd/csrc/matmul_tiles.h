@@ -28,6 +28,34 @@ __device__ inline void store_c(const MatmulP &p, int64_t row0, int64_t col0, con
     }
 }
 
+// The same for KG wavefronts on each block: their sums meet in LDS (`red`,
+// KG x BM x BN floats, free when this is called), and each thread adds and
+// stores elements of C row by row.
+template <int BM, int BN, int WM, int WN, int KG>
+__device__ inline void store_c_sum(const MatmulP &p, int64_t row0, int64_t col0, const f32x16 (&acc)[BM / WM / 32][BN / WN / 32],
+                                   float *red) {
+  constexpr int FM = BM / WM / 32, FN = BN / WN / 32, NTH = WM * WN * KG * 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kg = wave / (WM * WN), wt = wave % (WM * WN), wm = wt / WN, wn = wt % WN;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = wm * (BM / WM) + i * 32 + 8 * (r / 4) + 4 * (lane >> 5) + (r % 4);
+        red[(kg * BM + row) * BN + wn * (BN / WN) + j * 32 + (lane & 31)] = acc[i][j][r];
+      }
+  __syncthreads();
+  for (int e = threadIdx.x; e < BM * BN; e += NTH) {
+    float s = red[e];
+#pragma unroll
+    for (int h = 1; h < KG; ++h) s += red[h * BM * BN + e];
+    const int64_t row = row0 + e / BN, col = col0 + e % BN;
+    if (row < p.M && col < p.N) p.C[row * p.ldc + col] = s;
+  }
+}
+
 // Tiles owned by this team under the tiled schedule.
 template <class F>
 __device__ inline void for_team_tiles(const SchedK &S, F &&f) {

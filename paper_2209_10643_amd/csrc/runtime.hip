@@ -713,38 +713,50 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
     case UPIR_BODY_MATMUL_F32:
     case UPIR_BODY_MATMUL_BF16:
     case UPIR_BODY_MATMUL_SPLIT3: {
-      // MFMA tile configurations: bfloat16 and the split's three products
-      // 256 x 256 on 4 wavefronts of 128 x 128 each (the split as one product
-      // over K' = 3K: 250 us against 355 us for the 8-wavefront tile at
-      // 4096^3); 128 x 128 tiles when C has fewer 256 x 256 tiles than half
-      // the device's CUs (measured with 256 CUs: 128 x 128 faster at 2048^2,
-      // 64 large tiles; 256 x 256 faster at 3072^2, 144 large tiles).
-      // float32: the tile with the smallest estimate of (tiles per CU, rounded
-      // up) x (time of a tile per k, measured with every CU busy): 126 ns for
-      // 256 x 128 on 8 wavefronts, 70 for 128 x 128 on 4, 22 for 64 x 64 and
-      // 7.3 for 32 x 32 on 8 that share the k range (1024^3: 25 us on 64 x 64
-      // against 77 on 128 x 128; 512^3: 7 us on 32 x 32 against 14; 2000^3:
-      // 155 us on 128 x 128 against 186 on 64 x 64).
+      // The tile with the smallest estimate of (tiles per CU, rounded up) x K
+      // x (nanoseconds of a tile per k, measured with every CU busy), plus
+      // the pre-pass of the tiles that read bfloat16 operands from the
+      // workspace: 5 us and its bytes at 5.5 TB/s. `per` tiles of a kind run
+      // on a CU together. What it decides between, measured (us):
+      //   float32   512^3    7 (32 x 32)     14 (64 x 64)    41 (128 x 128)
+      //            1024^3   25 (64 x 64)     31 (32 x 32)    76 (128 x 128)
+      //            2000^3  152 (128 x 128)  170 (64 x 64)   262 (256 x 128)
+      //            4096^3 1027 (256 x 128) 1126 (128 x 128)
+      //   bfloat16  512^3    6 (32 x 32)      8 (64 x 64)    17 (pre-pass, 128 x 128)
+      //            2000^3   42 (128 x 128)   50 (pre-pass, 128 x 128)  56 (pre-pass, 256 x 256)
+      //            3000^3   90 (pre-pass, 256 x 256)        172 (128 x 128)
+      struct Tile {
+        int bm, bn, units, per;
+        bool pre;
+        double ns;
+      };
+      static const Tile f32[] = {{256, 128, 512, 1, false, 126.0}, {128, 128, 256, 1, false, 70.0},
+                                 {64, 64, 512, 1, false, 22.0}, {32, 32, 512, 1, false, 7.3}};
+      static const Tile bf16[] = {{256, 256, 256, 1, true, 22.0}, {128, 128, 256, 2, true, 20.0},
+                                  {128, 128, 512, 1, false, 19.0}, {64, 64, 512, 1, false, 10.5},
+                                  {32, 32, 512, 1, false, 5.0}};
+      static const Tile split[] = {{256, 256, 256, 1, true, 60.0}, {128, 128, 256, 2, true, 45.0},
+                                   {128, 128, 512, 1, false, 30.0}, {64, 64, 512, 1, false, 14.0},
+                                   {32, 32, 512, 1, false, 6.0}};
+      const bool is_f32 = lp->kind == UPIR_BODY_MATMUL_F32, is_split = lp->kind == UPIR_BODY_MATMUL_SPLIT3;
+      const Tile *tiles = is_f32 ? f32 : is_split ? split : bf16;
+      const int64_t M = lp->cnt[0], N = lp->cnt[1], K = ((const upir_matmul_args *)lp->args)->K;
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = 0;
-      sp.num_units = 256;
-      if (lp->kind == UPIR_BODY_MATMUL_F32) {
-        static const struct { int bm, bn, units; double ns; } tiles[] = {
-            {256, 128, 512, 126.0}, {128, 128, 256, 70.0}, {64, 64, 512, 22.0}, {32, 32, 512, 7.3}};
-        double best = 0.0;
-        for (const auto &t : tiles) {
-          const double cost = (double)cdiv(cdiv(lp->cnt[0], t.bm) * cdiv(lp->cnt[1], t.bn), c->num_cus) * t.ns;
-          if (sc.tile[0] == 0 || cost < best) {
-            best = cost;
-            sc.tile[0] = t.bm;
-            sc.tile[1] = t.bn;
-            sp.num_units = t.units;
-          }
+      double best = 0.0;
+      for (int i = 0; i < (is_f32 ? 4 : 5); ++i) {
+        const Tile &t = tiles[i];
+        // the 256 x 256 tile addresses each operand with 32-bit offsets
+        if (t.pre && t.bm == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;
+        double us = 1e-3 * t.ns * (double)K * (double)cdiv(cdiv(M, t.bm) * cdiv(N, t.bn), (int64_t)t.per * c->num_cus);
+        if (t.pre) us += 5.0 + (double)(M + N) * (double)K * (is_split ? 8.0 : 6.0) / 5.5e6;
+        if (sc.tile[0] == 0 || us < best) {
+          best = us;
+          sc.tile[0] = t.bm;
+          sc.tile[1] = t.bn;
+          sp.num_units = t.units;
         }
-        break;
       }
-      const bool small = 2 * cdiv(lp->cnt[0], 256) * cdiv(lp->cnt[1], 256) < c->num_cus;
-      sc.tile[0] = sc.tile[1] = small ? 128 : 256;
       break;
     }
     case UPIR_BODY_MATVEC:
@@ -1029,7 +1041,8 @@ upir_status launch_plan(upir_ctx *c, upir_loop_obj *lp, const Plan &pl, bool for
     case V_MATMUL_MFMA: {
       MatmulP p = *(const MatmulP *)pay;
       p.panel = matmul_wide(p, S) ? 1 : 0;  // the pre-pass writes the layout the tile reads
-      if (p.kind != UPIR_BODY_MATMUL_F32) e = launch_bf16_split(p, p.kind == UPIR_BODY_MATMUL_SPLIT3, c->stream);
+      if (p.kind != UPIR_BODY_MATMUL_F32 && !matmul_direct(p, S))
+        e = launch_bf16_split(p, p.kind == UPIR_BODY_MATMUL_SPLIT3, c->stream);
       if (e == hipSuccess) e = launch_matmul_mfma(p, pl.L, S, c->stream);
       break;
     }

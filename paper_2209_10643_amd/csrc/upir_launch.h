@@ -57,6 +57,9 @@ bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S);
 // float32 tiles for operands the above leaves out (any pitch and alignment); the schedule decides.
 bool mm_f32_supports(const MatmulP &p, const LoopK &L, const SchedK &S);
 hipError_t launch_mm_f32(const MatmulP &p, const SchedK &S, hipStream_t st);
+// bfloat16 tiles that read the float32 operands themselves (no pre-pass).
+bool matmul_direct(const MatmulP &p, const SchedK &S);
+hipError_t launch_mm_direct(const MatmulP &p, const SchedK &S, hipStream_t st);
 // BF16 pre-pass: A (M x K) -> ah, al; B (K x N) -> bh, bl transposed (N x K).
 hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st);
 // The 256 x 256 four-wavefront bfloat16 tile (it reads the k-panel workspace layout).

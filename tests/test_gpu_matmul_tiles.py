@@ -76,6 +76,36 @@ def test_f32_tiles(ctx, tile, units, M, N, K):
         assert np.array_equal(got.astype(np.float64), want), (off, pad)
 
 
+@pytest.mark.parametrize("kind", ["bf16", "split"])
+@pytest.mark.parametrize("tile,units", [((32, 32), 512), ((64, 64), 512), ((128, 128), 512), ((128, 128), 256),
+                                        ((256, 256), 256), ((256, 256), 512), ((16, 16), 64), (None, 0)])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_bf16_tiles(ctx, kind, tile, units, M, N, K):
+    """The tiles that read float32 operands themselves, those behind the
+    pre-pass (K no multiple of eight: the workspace's last chunk of k is
+    padded) and the schedule-exact kernel."""
+    print(f"{kind} {M}x{N}x{K} tile={tile} units={units}", flush=True)
+    rng = np.random.default_rng(M * N + K)
+    A, B = (rng.integers(-2, 3, s).astype(np.float32) for s in ((M, K), (K, N)))
+    want = bodies.matmul(A, B)
+    for off, pad, teams in ((0, 0, 0), (1, 3, 2)):
+        s = H.make_sched(U.UPIR_SCHED_STATIC, tile=tile) if tile else None
+        got = product(ctx, kind, A, B, s, H.make_spmd(teams, units), off, pad)
+        assert np.array_equal(got.astype(np.float64), want), (off, pad)
+
+
+@pytest.mark.parametrize("units", [256, 512])
+def test_split_keeps_its_low_parts(ctx, units):
+    """1 + 2^-9 has a low part: the product of the rounded operands alone is
+    off by 2^-8 of each entry."""
+    M, N, K = 70, 66, 45
+    A, B = np.full((M, K), 1 + 2.0 ** -9, np.float32), np.ones((K, N), np.float32)
+    B[::2] = -(1 + 2.0 ** -9)
+    for tile in ((128, 128),) + (((64, 64), (32, 32)) if units == 512 else ((256, 256),)):
+        got = product(ctx, "split", A, B, H.make_sched(U.UPIR_SCHED_STATIC, tile=tile), H.make_spmd(0, units))
+        assert bodies.frob_rel(got, bodies.matmul_split3(A, B)) <= 1e-5
+
+
 def test_pending_fold_before_an_unaligned_product(ctx):
     """An async sum's fold is pending when a product that takes no fold along
     runs: the sum is delivered, the product is right."""
