@@ -583,6 +583,7 @@ static const MMConf kMM[] = {
     {UPIR_BODY_MATMUL_BF16, 128, 128, 512}, {UPIR_BODY_MATMUL_SPLIT3, 128, 128, 512},
     {UPIR_BODY_MATMUL_BF16, 64, 64, 512}, {UPIR_BODY_MATMUL_SPLIT3, 64, 64, 512},
     {UPIR_BODY_MATMUL_BF16, 32, 32, 512}, {UPIR_BODY_MATMUL_SPLIT3, 32, 32, 512},
+    {UPIR_BODY_MATMUL_F32, 64, 128, 512}, {UPIR_BODY_MATMUL_BF16, 64, 128, 512}, {UPIR_BODY_MATMUL_SPLIT3, 64, 128, 512},
 };
 
 bool matmul_mfma_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {

@@ -216,13 +216,18 @@ static hipError_t go_direct(const MatmulP &p, const SchedK &S, hipStream_t st) {
 
 // 128 x 128 on 512 units (on 256 units that tile reads the pre-pass workspace).
 bool matmul_direct(const MatmulP &p, const SchedK &S) {
-  return p.kind != UPIR_BODY_MATMUL_F32 && S.U == 512 && S.tile[0] == S.tile[1] && S.tile[0] <= 128;
+  const int bm = S.tile[0], bn = S.tile[1];
+  return p.kind != UPIR_BODY_MATMUL_F32 && S.U == 512 &&
+         ((bm == 128 && bn == 128) || (bm == 64 && (bn == 64 || bn == 128)) || (bm == 32 && bn == 32));
 }
 
 template <int NPROD>
 static hipError_t go_direct_tile(const MatmulP &p, const SchedK &S, hipStream_t st) {
   if (S.tile[0] == 128) return go_direct<NPROD, 128, 128, 2, 4, 1, 32>(p, S, st);
-  if (S.tile[0] == 64) return go_direct<NPROD, 64, 64, 2, 1, 4, 64>(p, S, st);
+  if (S.tile[0] == 64) {
+    if (S.tile[1] == 128) return go_direct<NPROD, 64, 128, 2, 2, 2, 64>(p, S, st);
+    return go_direct<NPROD, 64, 64, 2, 1, 4, 64>(p, S, st);
+  }
   return go_direct<NPROD, 32, 32, 1, 1, 8, 128>(p, S, st);
 }
 

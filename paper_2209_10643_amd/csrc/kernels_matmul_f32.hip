@@ -234,13 +234,16 @@ bool mm_f32_supports(const MatmulP &p, const LoopK &L, const SchedK &S) {
   if (L.lb[0] != 0 || L.lb[1] != 0) return false;
   const int bm = S.tile[0], bn = S.tile[1];
   return (bm == 256 && bn == 128 && S.U == 512) || (bm == 128 && bn == 128 && S.U == 256) ||
-         (bm == 64 && bn == 64 && S.U == 512) || (bm == 32 && bn == 32 && S.U == 512);
+         (S.U == 512 && ((bm == 64 && (bn == 64 || bn == 128)) || (bm == 32 && bn == 32)));
 }
 
 hipError_t launch_mm_f32(const MatmulP &p, const SchedK &S, hipStream_t st) {
   if (S.tile[0] == 256) return go_f32<256, 128, 4, 2, 1, 32>(p, S, st);
   if (S.tile[0] == 128) return go_f32<128, 128, 2, 2, 1, 32>(p, S, st);
-  if (S.tile[0] == 64) return go_f32<64, 64, 2, 1, 4, 32>(p, S, st);
+  if (S.tile[0] == 64) {
+    if (S.tile[1] == 128) return go_f32<64, 128, 2, 2, 2, 32>(p, S, st);
+    return go_f32<64, 64, 2, 1, 4, 32>(p, S, st);
+  }
   return go_f32<32, 32, 1, 1, 8, 64>(p, S, st);
 }
 

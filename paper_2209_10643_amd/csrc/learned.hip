@@ -621,6 +621,7 @@ static std::vector<Cand> candidates(upir_ctx *c, const upir_loop_obj *lp) {
     case UPIR_BODY_MATMUL_F32:
       add(0, 256, UPIR_SCHED_STATIC, 0, 128, 128);
       add(0, 512, UPIR_SCHED_STATIC, 0, 256, 128);
+      add(0, 512, UPIR_SCHED_STATIC, 0, 64, 128);
       add(0, 512, UPIR_SCHED_STATIC, 0, 64, 64);
       add(0, 512, UPIR_SCHED_STATIC, 0, 32, 32);
       break;
@@ -630,6 +631,7 @@ static std::vector<Cand> candidates(upir_ctx *c, const upir_loop_obj *lp) {
       add(0, 256, UPIR_SCHED_STATIC, 0, 256, 256);
       add(0, 512, UPIR_SCHED_STATIC, 0, 256, 256);
       for (int t : {128, 64, 32}) add(0, 512, UPIR_SCHED_STATIC, 0, t, t);
+      add(0, 512, UPIR_SCHED_STATIC, 0, 64, 128);
       break;
     default:
       for (int32_t U : {64, 256}) add(teams(n, U * 4), U, UPIR_SCHED_STATIC, 0);

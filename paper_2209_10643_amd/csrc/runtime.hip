@@ -723,6 +723,7 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       //            2000^3  152 (128 x 128)  170 (64 x 64)   262 (256 x 128)
       //            4096^3 1027 (256 x 128) 1126 (128 x 128)
       //   bfloat16  512^3    6 (32 x 32)      8 (64 x 64)    17 (pre-pass, 128 x 128)
+      //   1000x1300x777   17 (64 x 128)     21 (128 x 128)   22 (64 x 64)
       //            2000^3   42 (128 x 128)   50 (pre-pass, 128 x 128)  56 (pre-pass, 256 x 256)
       //            3000^3   90 (pre-pass, 256 x 256)        172 (128 x 128)
       struct Tile {
@@ -731,12 +732,12 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         double ns;
       };
       static const Tile f32[] = {{256, 128, 512, 1, false, 126.0}, {128, 128, 256, 1, false, 70.0},
-                                 {64, 64, 512, 1, false, 22.0}, {32, 32, 512, 1, false, 7.3}};
+                                 {64, 128, 512, 1, false, 37.0}, {64, 64, 512, 1, false, 22.0}, {32, 32, 512, 1, false, 7.3}};
       static const Tile bf16[] = {{256, 256, 256, 1, true, 22.0}, {128, 128, 256, 2, true, 20.0},
-                                  {128, 128, 512, 1, false, 19.0}, {64, 64, 512, 1, false, 10.5},
+                                  {128, 128, 512, 1, false, 19.0}, {64, 128, 512, 1, false, 14.0}, {64, 64, 512, 1, false, 10.5},
                                   {32, 32, 512, 1, false, 5.0}};
       static const Tile split[] = {{256, 256, 256, 1, true, 60.0}, {128, 128, 256, 2, true, 45.0},
-                                   {128, 128, 512, 1, false, 30.0}, {64, 64, 512, 1, false, 14.0},
+                                   {128, 128, 512, 1, false, 30.0}, {64, 128, 512, 1, false, 22.0}, {64, 64, 512, 1, false, 14.0},
                                    {32, 32, 512, 1, false, 6.0}};
       const bool is_f32 = lp->kind == UPIR_BODY_MATMUL_F32, is_split = lp->kind == UPIR_BODY_MATMUL_SPLIT3;
       const Tile *tiles = is_f32 ? f32 : is_split ? split : bf16;
@@ -744,7 +745,7 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = 0;
       double best = 0.0;
-      for (int i = 0; i < (is_f32 ? 4 : 5); ++i) {
+      for (int i = 0; i < (is_f32 ? 5 : 6); ++i) {
         const Tile &t = tiles[i];
         // the 256 x 256 tile addresses each operand with 32-bit offsets
         if (t.pre && t.bm == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;

@@ -62,7 +62,8 @@ def product(ctx, kind, A, B, sched=None, spmd=None, off=0, pad=0):
 SHAPES = [(1, 1, 1), (5, 3, 2), (31, 33, 7), (33, 31, 64), (65, 66, 63), (64, 64, 128), (100, 130, 129), (130, 67, 321)]
 
 
-@pytest.mark.parametrize("tile,units", [((32, 32), 512), ((64, 64), 512), ((128, 128), 256), ((256, 128), 512), (None, 0)])
+@pytest.mark.parametrize("tile,units", [((32, 32), 512), ((64, 64), 512), ((64, 128), 512), ((128, 128), 256),
+                                        ((256, 128), 512), (None, 0)])
 @pytest.mark.parametrize("M,N,K", SHAPES)
 def test_f32_tiles(ctx, tile, units, M, N, K):
     print(f"f32 {M}x{N}x{K} tile={tile}", flush=True)
@@ -77,7 +78,8 @@ def test_f32_tiles(ctx, tile, units, M, N, K):
 
 
 @pytest.mark.parametrize("kind", ["bf16", "split"])
-@pytest.mark.parametrize("tile,units", [((32, 32), 512), ((64, 64), 512), ((128, 128), 512), ((128, 128), 256),
+@pytest.mark.parametrize("tile,units", [((32, 32), 512), ((64, 64), 512), ((64, 128), 512), ((128, 128), 512),
+                                        ((128, 128), 256),
                                         ((256, 256), 256), ((256, 256), 512), ((16, 16), 64), (None, 0)])
 @pytest.mark.parametrize("M,N,K", SHAPES)
 def test_bf16_tiles(ctx, kind, tile, units, M, N, K):
