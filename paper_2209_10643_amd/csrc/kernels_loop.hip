@@ -66,17 +66,16 @@ struct BMatmul {
   MatmulP p;
   __device__ void operator()(int64_t, const int64_t *iv, int, int, Acc &, int) const {
     const int64_t i = iv[0], j = iv[1];
-    const int64_t kp = mm_kpad(p.K);  // workspace rows
     float acc = 0.0f;
     if (p.kind == 4) {
       for (int64_t k = 0; k < p.K; ++k) acc = __builtin_fmaf(p.A[i * p.lda + k], p.B[k * p.ldb + j], acc);
     } else if (p.kind == 5) {
       for (int64_t k = 0; k < p.K; ++k)
-        acc = __builtin_fmaf(bf16_to_f32(p.ah[i * kp + k]), bf16_to_f32(p.bh[j * kp + k]), acc);
+        acc = __builtin_fmaf(bf16_to_f32(p.ah[i * p.K + k]), bf16_to_f32(p.bh[j * p.K + k]), acc);
     } else {
       for (int64_t k = 0; k < p.K; ++k) {
-        const float ah = bf16_to_f32(p.ah[i * kp + k]), al = bf16_to_f32(p.al[i * kp + k]);
-        const float bh = bf16_to_f32(p.bh[j * kp + k]), bl = bf16_to_f32(p.bl[j * kp + k]);
+        const float ah = bf16_to_f32(p.ah[i * p.K + k]), al = bf16_to_f32(p.al[i * p.K + k]);
+        const float bh = bf16_to_f32(p.bh[j * p.K + k]), bl = bf16_to_f32(p.bl[j * p.K + k]);
         acc = __builtin_fmaf(al, bh, acc);
         acc = __builtin_fmaf(ah, bl, acc);
         acc = __builtin_fmaf(ah, bh, acc);
@@ -213,7 +212,9 @@ hipError_t launch_generic(int32_t body, const void *payload, const LoopK &L, con
       }
       return hipErrorInvalidValue;
     }
-    case 3: return go_generic(BJacobi{*(const JacobiP *)payload}, L, S, R, st);
+    case 3:
+      if (jacobi_strips_support(*(const JacobiP *)payload, L, S)) return launch_jacobi_tile(*(const JacobiP *)payload, L, S, R, st);
+      return go_generic(BJacobi{*(const JacobiP *)payload}, L, S, R, st);
     case 4:
       if (mm_f32_supports(*(const MatmulP *)payload, L, S)) {
         if (R.fold.count > 0) {  // these tiles take no fold along
@@ -542,8 +543,8 @@ __device__ __forceinline__ void jacobi_strip(const float *sp, float *dp, int ld,
       if (RED) acc.add4(v, mid, mk);
       if (!EDGE) {
         float *out = dp + __builtin_amdgcn_readfirstlane((r + q) * ld) + cl;
-        if (NT) __builtin_nontemporal_store(v, (f32x4 *)out);
-        else *(f32x4 *)out = v;
+        if (NT) __builtin_nontemporal_store(v, (f32x4u *)out);
+        else *(f32x4u *)out = v;
       } else {
         const int soff = __builtin_amdgcn_readfirstlane((r + q) * (int)rowb);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rd, so4, soff, 0);
@@ -602,7 +603,7 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   ResidualAcc<RED> acc;
 
   auto do_tile = [&](int64_t m) {
-    const int64_t ti = S.t0[0] + m / S.nt[1], tj = S.t0[1] + m % S.nt[1];
+    const int64_t mi = quot(m, S.nt[1]), ti = S.t0[0] + mi, tj = S.t0[1] + (m - mi * S.nt[1]);
     const int64_t i0 = ti * TH, j0 = tj * JT_W;
     const int64_t s0 = i0 + (int64_t)w * SH, s1 = s0 + SH < i0 + TH ? s0 + SH : i0 + TH;
     const int64_t ra = s0 > ilo ? s0 : ilo, rb = s1 < ihi ? s1 : ihi;
@@ -631,7 +632,11 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   if (RED) finish_reduction<double>(R, acc.m64);
 }
 
-bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S) {
+// The schedules and boxes the strips run, whatever the grid's pitch and
+// alignment (16-byte accesses at any element; a pitch that is no multiple of
+// four used to leave them for the schedule-exact kernel: 29 us for a sweep of
+// 1501 x 2003).
+bool jacobi_strips_support(const JacobiP &p, const LoopK &L, const SchedK &S) {
   if (L.nd != 2 || !S.tiled || S.dist != DIST_TU) return false;
   if (L.step[0] != 1 || L.step[1] != 1) return false;
   if (S.tile[1] != JT_W) return false;
@@ -639,10 +644,12 @@ bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S) {
   if (th != 4 && th != 8 && th != 16 && th != 32 && th != 64 && th != 128) return false;
   if (S.U % WAVE != 0 || S.U < WAVE) return false;
   if (S.policy != POL_STATIC && S.policy != POL_CHUNK) return false;
-  if ((p.ld % 4) != 0 || ((uintptr_t)p.src % 16) != 0 || ((uintptr_t)p.dst % 16) != 0) return false;
   if (L.lb[1] < 1 || L.lb[0] < 1) return false;  // halo reads at lb-1 stay in the array
   if ((int64_t)(th + 2) * p.ld * 4 + 2048 >= (1LL << 31)) return false;  // 32-bit byte offsets within a strip
   return true;
+}
+bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S) {
+  return jacobi_strips_support(p, L, S) && (p.ld % 4) == 0 && ((uintptr_t)p.src % 16) == 0 && ((uintptr_t)p.dst % 16) == 0;
 }
 
 template <bool NT>
@@ -772,7 +779,7 @@ __global__ void __launch_bounds__(1024) k_filter7_tile(LoopK L, SchedK S, Filter
 #pragma unroll
   for (int i = 0; i < 49; ++i) wk[i] = p.w[i];
   auto do_tile = [&](int64_t m) {
-    const int64_t ti = S.t0[0] + m / S.nt[1], tj = S.t0[1] + m % S.nt[1];
+    const int64_t mi = quot(m, S.nt[1]), ti = S.t0[0] + mi, tj = S.t0[1] + (m - mi * S.nt[1]);
     const int64_t i0 = ti * TH, j0 = tj * JT_W;
     const int64_t s0 = i0 + (int64_t)w * SH, s1 = s0 + SH < i0 + TH ? s0 + SH : i0 + TH;
     const int64_t ra = s0 > ilo ? s0 : ilo, rb = s1 < ihi ? s1 : ihi;

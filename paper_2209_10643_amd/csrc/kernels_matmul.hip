@@ -18,19 +18,21 @@ __device__ inline uint16_t to_bf16_rne(float x) {
 __device__ inline float bf16f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // Workspace element (row, k) of an operand with `rows` rows: rows of K
-// rounded up to 32 (layout 0), or k-panels of 32 (layout 1): panel k / 32
-// holds 32 k of every row, row after row, so the rows x 32 block one k step
-// reads is contiguous. In both, the chunk of eight k that holds k = K - 1 is
-// filled up with zeros, so the tiles read whole chunks for any K.
+// (layout 0, the schedule-exact kernel's), rows of K rounded up to 32 (layout
+// 2), or k-panels of 32 (layout 1): panel k / 32 holds 32 k of every row, row
+// after row, so the rows x 32 block one k step reads is contiguous. In the
+// layouts the tiles read (1 and 2) the chunk of eight k that holds k = K - 1
+// is filled up with zeros, so they read whole chunks for any K.
 __device__ inline int64_t ws_index(int panel, int64_t row, int64_t k, int64_t rows, int64_t K) {
-  return panel ? (((k >> 5) * rows + row) << 5) + (k & 31) : row * mm_kpad(K) + k;
+  if (panel == 1) return (((k >> 5) * rows + row) << 5) + (k & 31);
+  return row * (panel ? mm_kpad(K) : K) + k;
 }
 
-// Element forms (workspace off a 16-byte boundary): every k up to the end of
-// the last chunk of eight. A (M x K, lda) -> ah / al, row-major, coalesced.
+// Element forms (workspace off a 16-byte boundary, or layout 0 with K no
+// multiple of eight): every k up to the end of the last chunk of eight. A (M x K, lda) -> ah / al, row-major, coalesced.
 __global__ void __launch_bounds__(256) k_split_rows(const float *__restrict__ A, int64_t M, int64_t K, int64_t lda,
                                                     uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int panel) {
-  const int64_t KE = (K + 7) / 8 * 8, total = M * KE;
+  const int64_t KE = panel ? (K + 7) / 8 * 8 : K, total = M * KE;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = e / KE, k = e - i * KE, d = ws_index(panel, i, k, M, K);
     const float x = k < K ? A[i * lda + k] : 0.0f;
@@ -44,7 +46,8 @@ __global__ void __launch_bounds__(256) k_split_rows(const float *__restrict__ A,
 __global__ void __launch_bounds__(256) k_split_cols(const float *__restrict__ B, int64_t K, int64_t N, int64_t ldb,
                                                     uint16_t *__restrict__ hi, uint16_t *__restrict__ lo, int panel) {
   __shared__ float t[64][65];
-  const int64_t k0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64, KE = (K + 7) / 8 * 8;
+  const int64_t k0 = (int64_t)blockIdx.y * 64, n0 = (int64_t)blockIdx.x * 64;
+  const int64_t KE = panel ? (K + 7) / 8 * 8 : K;
   const int tx = threadIdx.x % 64, ty = threadIdx.x / 64;  // 64 x 4
   for (int r = ty; r < 64; r += 4) {
     const int64_t k = k0 + r, n = n0 + tx;
@@ -140,8 +143,8 @@ __global__ void __launch_bounds__(256) k_split_cols8(const float *__restrict__ B
 }
 
 hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st) {
-  // vector forms: 16-byte aligned workspace arrays
-  const bool vec = (uintptr_t)p.ah % 16 == 0 && (uintptr_t)p.bh % 16 == 0 &&
+  // vector forms: 16-byte aligned workspace arrays and rows
+  const bool vec = (p.panel || p.K % 8 == 0) && (uintptr_t)p.ah % 16 == 0 && (uintptr_t)p.bh % 16 == 0 &&
                    (!need_lo || ((uintptr_t)p.al % 16 == 0 && (uintptr_t)p.bl % 16 == 0));
   if (p.M > 0 && p.K > 0) {
     if (vec) {
@@ -242,7 +245,7 @@ __global__ void __launch_bounds__(WM * WN * 64) k_mm_bf16(MatmulP p, SchedK S) {
   const int64_t K = p.K, KP = mm_kpad(K);
 
   for_team_tiles(S, [&](int64_t m) {
-    const int64_t row0 = (S.t0[0] + m / S.nt[1]) * BM, col0 = (S.t0[1] + m % S.nt[1]) * BN;
+    const int64_t mi = quot(m, S.nt[1]), row0 = (S.t0[0] + mi) * BM, col0 = (S.t0[1] + (m - mi * S.nt[1])) * BN;
     f32x16 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -438,9 +441,9 @@ __global__ void __launch_bounds__(256) k_mm_bf16_wide(MatmulP p, SchedK S) {
   for_team_tiles(S, [&](int64_t m) {
     // grouped tile order: groups of G tile rows, column-major inside a group
     const int64_t nt0 = S.nt[0], nt1 = S.nt[1], G = 4;
-    const int64_t grp = m / (G * nt1), in = m - grp * G * nt1;
+    const int64_t grp = quot(m, G * nt1), in = m - grp * G * nt1;
     const int64_t gsz = std::min<int64_t>(G, nt0 - grp * G);
-    const int64_t trow = grp * G + in % gsz, tcol = in / gsz;
+    const int64_t tcol = quot(in, gsz), trow = grp * G + (in - tcol * gsz);
     const int64_t row0 = (S.t0[0] + trow) * BM, col0 = (S.t0[1] + tcol) * BM;
     f32x16 acc[4][4];
 #pragma unroll

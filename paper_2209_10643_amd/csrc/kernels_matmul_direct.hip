@@ -48,7 +48,7 @@ __global__ void __launch_bounds__(WM * WN * KG * 64) k_mm_direct(MatmulP p, Sche
   const int64_t K = p.K;
 
   for_team_tiles(S, [&](int64_t m) {
-    const int64_t row0 = (S.t0[0] + m / S.nt[1]) * BM, col0 = (S.t0[1] + m % S.nt[1]) * BN;
+    const int64_t mi = quot(m, S.nt[1]), row0 = (S.t0[0] + mi) * BM, col0 = (S.t0[1] + (m - mi * S.nt[1])) * BN;
     f32x16 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)

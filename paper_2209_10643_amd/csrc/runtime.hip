@@ -694,16 +694,34 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       break;
     case UPIR_BODY_JACOBI5:
     case UPIR_BODY_FILTER7: {
-      // the tallest tile (longest wavefront strips) that still gives every
-      // SIMD four wavefronts: at least 4 x CUs tiles of 4 wavefronts each
-      // (128-row tiles: Jacobi only)
+      // Tiles of 4 wavefronts, the tallest (longest strips, fewest re-read
+      // rows) that still keeps the device busy. Up to 32 rows 1.5 x CUs tiles
+      // are enough (sweeps of 1501 x 2003, maximum taken: 12.5 us with 752
+      // tiles of 16 rows, 13.1 with 376 of 32, 14.9 with 1504 of 8; 1000 x
+      // 1001: 9.2 with 500 of 8, 10.9 with 1000 of 4). Without a residual
+      // strips of more than 4 rows only lengthen each wavefront's chain (4096
+      // x 4096: 21.1 us on 16 rows, 23.0 on 64). With one, 64 rows are worth
+      // it where the tiles fill the 4 x CUs resident ones once, or often
+      // enough that the last round does not count (4096 x 4096 24.1 us async
+      // against 24.5 on 32; 4833 x 5992, 1.8 rounds, 40.7 against 38.0), and
+      // 128 where the grids leave the last-level cache (16384 x 16384: 407 us
+      // against 430). The filter keeps 4 x CUs tiles.
       sc.policy = UPIR_SCHED_STATIC;
       sc.tile[1] = 256;
       sc.tile[0] = 4;
-      const int64_t ct = cdiv(std::max<int64_t>(lp->cnt[1], 1), 256);
+      const int64_t ct = cdiv(std::max<int64_t>(lp->cnt[1], 1), 256), rows = std::max<int64_t>(lp->cnt[0], 1);
+      const int64_t cus = c->num_cus;
+      const bool filter = lp->kind == UPIR_BODY_FILTER7;
+      auto enough = [&](int th) {
+        const int64_t tiles = cdiv(rows, th) * ct;
+        if (filter) return th <= 64 && tiles >= 4 * cus;
+        if (th > 16 && !lp->has_red) return false;
+        if (th == 128) return tiles >= 8 * cus;
+        if (th == 64) return (tiles >= 4 * cus && 16 * tiles <= 17 * 4 * cus) || tiles >= 12 * cus;
+        return 2 * tiles >= 3 * cus;
+      };
       for (int th : {128, 64, 32, 16, 8})
-        if ((th < 128 || lp->kind == UPIR_BODY_JACOBI5) &&
-            cdiv(std::max<int64_t>(lp->cnt[0], 1), th) * ct >= 4LL * c->num_cus) {
+        if (enough(th)) {
           sc.tile[0] = th;
           break;
         }
@@ -1041,7 +1059,7 @@ upir_status launch_plan(upir_ctx *c, upir_loop_obj *lp, const Plan &pl, bool for
     case V_MATVEC_WAVE: e = launch_matvec_wave(*(const MatvecP *)pay, pl.L, S, R, c->stream); break;
     case V_MATMUL_MFMA: {
       MatmulP p = *(const MatmulP *)pay;
-      p.panel = matmul_wide(p, S) ? 1 : 0;  // the pre-pass writes the layout the tile reads
+      p.panel = matmul_wide(p, S) ? 1 : 2;  // the pre-pass writes the layout the tile reads
       if (p.kind != UPIR_BODY_MATMUL_F32 && !matmul_direct(p, S))
         e = launch_bf16_split(p, p.kind == UPIR_BODY_MATMUL_SPLIT3, c->stream);
       if (e == hipSuccess) e = launch_matmul_mfma(p, pl.L, S, c->stream);

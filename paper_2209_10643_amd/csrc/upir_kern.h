@@ -77,8 +77,20 @@ constexpr unsigned long long SLOT_EMPTY = ~0ULL;
 constexpr int SLOT_WORDS = 16;  // 64-bit words between slots
 
 // ------------------------------------------------------------------ helpers
+// a / b for a >= 0, b > 0. A 64-bit division is some 150 instructions in a
+// row on this part, a 32-bit one 20, and a tile kernel starts with three (the
+// smallest tiled launches: 9.1 to 9.0 and 5.7 to 5.6 us).
+__host__ __device__ inline int64_t quot(int64_t a, int64_t b) {
+  if (((uint64_t)(a | b) >> 32) == 0) return (int64_t)((uint32_t)a / (uint32_t)b);
+  return a / b;
+}
 __host__ __device__ inline void block_range(int64_t n, int64_t parts, int64_t p, int64_t &lo, int64_t &hi) {
-  int64_t q = n / parts, r = n % parts;
+  if (n == parts) {  // one each, as in a launch with one team per tile
+    lo = p;
+    hi = p + 1;
+    return;
+  }
+  const int64_t q = quot(n, parts), r = n - q * parts;
   lo = p * q + (p < r ? p : r);
   hi = lo + q + (p < r ? 1 : 0);
 }
