@@ -705,7 +705,11 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // enough that the last round does not count (4096 x 4096 24.1 us async
       // against 24.5 on 32; 4833 x 5992, 1.8 rounds, 40.7 against 38.0), and
       // 128 where the grids leave the last-level cache (16384 x 16384: 407 us
-      // against 430). The filter keeps 4 x CUs tiles.
+      // against 430). The filter brings six more rows per tile into
+      // LDS and takes 2 x CUs tiles (1024 x 1024: 6.6 us on 8 rows, 7.4 on 4;
+      // 1001 x 1501: 8.0 on 8, 8.7 on 16, 10.3 on 4), 32 rows from 4 x CUs
+      // tiles on (2048 x 2048: 12.2 us on 16, 12.4 on 32; 8192 x 8192: 136 on
+      // 32, 146 on 16, 150 on 64).
       sc.policy = UPIR_SCHED_STATIC;
       sc.tile[1] = 256;
       sc.tile[0] = 4;
@@ -714,7 +718,7 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       const bool filter = lp->kind == UPIR_BODY_FILTER7;
       auto enough = [&](int th) {
         const int64_t tiles = cdiv(rows, th) * ct;
-        if (filter) return th <= 64 && tiles >= 4 * cus;
+        if (filter) return th <= 32 && tiles >= (th == 32 ? 4 : 2) * cus;
         if (th > 16 && !lp->has_red) return false;
         if (th == 128) return tiles >= 8 * cus;
         if (th == 64) return (tiles >= 4 * cus && 16 * tiles <= 17 * 4 * cus) || tiles >= 12 * cus;

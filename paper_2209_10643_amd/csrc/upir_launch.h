@@ -65,9 +65,10 @@ hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st);
 // The 256 x 256 four-wavefront bfloat16 tile (it reads the k-panel workspace layout).
 bool matmul_wide(const MatmulP &p, const SchedK &S);
 
-// Tiled Jacobi kernel: what its strips run at all, and what is reported as
-// the tiled variant (16-byte aligned rows as well).
+// Tiled Jacobi and filter kernels: what they run at all, and what is
+// reported as the tiled variant (16-byte aligned rows as well).
 bool jacobi_strips_support(const JacobiP &p, const LoopK &L, const SchedK &S);
+bool filter7_strips_support(const Filter7P &p, const LoopK &L, const SchedK &S);
 bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S);
 bool filter7_tile_supports(const Filter7P &p, const LoopK &L, const SchedK &S);
 

@@ -1,4 +1,4 @@
-"""GPU parity of the tiled Jacobi strips on grids whose
+"""GPU parity of the tiled Jacobi and 7 x 7 filter strips on grids whose
 pitch is no multiple of four and whose first element is off a 16-byte
 boundary: bit for bit against the oracle, for tiles ragged on all sides, one
 or two columns, every tile height and one or several wavefronts per tile;
@@ -64,3 +64,27 @@ def test_jacobi(ctx, shape, th, units):
             assert np.array_equal(out[at:at + u.size].reshape(shape), want)
             assert (out[:at] == -7).all() and (out[at + u.size:] == -7).all()
             assert r.item() == res
+
+
+@pytest.mark.parametrize("th,units", SCHEDS)
+@pytest.mark.parametrize("shape", SHAPES)
+def test_filter7(ctx, shape, th, units):
+    print(f"filter7 {shape} tile {th} units {units}", flush=True)
+    rows, cols = shape
+    u = synth.uniform_pm1(62, 0, rows * cols).reshape(shape)
+    w = synth.uniform_pm1(62, 1, 49).reshape(7, 7) * np.float32(0.25)
+    want = bodies.filter7(u, w, np.full(shape, -7.0, np.float32))
+    tw = torch.from_numpy(w).cuda()
+    sched = H.make_sched(U.UPIR_SCHED_STATIC, tile=(th, 256)) if th else None
+    for off in (0, 1, 3):
+        src, ps = placed(u, off)
+        dst, pd = placed(np.full(shape, -7.0, np.float32), (off + 2) % 4)
+        lp = ctx.loop(U.UPIR_BODY_FILTER7, U.upir_filter7_args(ps, pd, tw.data_ptr(), cols),
+                      [(3, rows - 3, 1), (3, cols - 3, 1)], sched)
+        ctx.launch(lp, H.make_spmd(0, units))
+        ctx.sync()
+        ctx.free(lp)
+        out = dst.cpu().numpy()
+        at = (off + 2) % 4
+        assert np.array_equal(out[at:at + u.size].reshape(shape), want)
+        assert (out[:at] == -7).all() and (out[at + u.size:] == -7).all()
