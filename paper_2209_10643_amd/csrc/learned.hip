@@ -11,8 +11,9 @@
 //    row per (loop, candidate) goes into the context's timing table.
 //  * Cost model: an MLP 32 -> 64 -> 64 -> 1 (float32) predicts log2(time in
 //    microseconds) from 32 features of (loop, candidate). It is trained on
-//    the timing table by this file's own kernels: forward, backward (per-row
-//    deltas, then one thread per parameter summing rows in order) and Adam.
+//    the timing table by this file's own kernels: one over the rows (forward
+//    and backward, each wavefront summing its rows' gradients), one over the
+//    parameters (sum over the wavefronts, Adam).
 #include <math.h>
 #include <stdio.h>
 #include <string.h>
@@ -30,124 +31,237 @@ constexpr int F = 32, H1 = 64, H2 = 64;
 constexpr int O_W1 = 0, O_B1 = O_W1 + H1 * F, O_W2 = O_B1 + H1, O_B2 = O_W2 + H2 * H1, O_W3 = O_B2 + H2,
               O_B3 = O_W3 + H2, NP = O_B3 + 1;
 static_assert(NP == UPIR_MLP_PARAMS, "parameter count");
+constexpr int MLP_PART = (NP + 1 + 63) / 64 * 64;  // floats per wavefront: gradients, squared error
+constexpr int MLP_WAVES = 512;                     // wavefronts of a training step at most
+static_assert(H1 == 64 && H2 == 64 && O_W2 % 4 == 0, "a lane is a hidden unit; rows of weights are read by four");
 
 // ------------------------------------------------------------------ kernels
-// Forward pass, one row per thread, parameters staged in LDS. Optionally
-// keeps the pre-activations z1, z2 of every row for the backward pass.
-__global__ void __launch_bounds__(256) k_mlp_fwd(const float *__restrict__ X, int64_t n, const float *__restrict__ P,
-                                                 float *__restrict__ Y, float *__restrict__ Z1, float *__restrict__ Z2) {
-  __shared__ float sp[NP];
-  for (int i = threadIdx.x; i < NP; i += blockDim.x) sp[i] = P[i];
-  __syncthreads();
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  float x[F], h1[H1];
-  for (int k = 0; k < F; ++k) x[k] = X[r * F + k];
-  for (int j = 0; j < H1; ++j) {
-    float z = sp[O_B1 + j];
-    for (int k = 0; k < F; ++k) z = __builtin_fmaf(sp[O_W1 + j * F + k], x[k], z);
-    if (Z1) Z1[r * H1 + j] = z;
-    h1[j] = z > 0.0f ? z : 0.0f;
-  }
-  float y = sp[O_B3];
-  for (int j = 0; j < H2; ++j) {
-    float z = sp[O_B2 + j];
-    for (int k = 0; k < H1; ++k) z = __builtin_fmaf(sp[O_W2 + j * H1 + k], h1[k], z);
-    if (Z2) Z2[r * H2 + j] = z;
-    y = __builtin_fmaf(sp[O_W3 + j], z > 0.0f ? z : 0.0f, y);
-  }
-  Y[r] = y;
-}
+// Rows of the network, forward and (TRAIN) backward. A workgroup is one
+// wavefront and lane j is hidden unit j of both layers: it keeps row j of W1
+// and W2 (and column j of W2) in registers and takes rows of X from a
+// grid-strided loop, MLP_R at a time. A row's values, the first layer's
+// activations and the second's deltas reach every lane through LDS, four per
+// read. Pre-activations are sums over k in order, from
+// the bias, as a thread per row computed them. TRAIN also sums this
+// wavefront's gradients in registers (row j of both weight matrices) and
+// leaves them, and its squared error, as row blockIdx.x of `part`.
+//
+// At these sizes (6,208 multiply-adds a row) time is latency: one thread per
+// row, its activations indexed in scratch memory, took 41 us for the forward
+// pass of 256 rows, 42 for the row deltas, and a thread per parameter walking
+// the batch 68 us; this kernel takes 6 for the same rows.
+constexpr int MLP_R = 4;
+typedef float f32x4m __attribute__((ext_vector_type(4)));
+typedef float f32x16m __attribute__((ext_vector_type(16)));
 
-// Per-row deltas: dy = 2 (y - t) / B, dz2 = dy W3 * [z2 > 0],
-// dz1 = (dz2 W2) * [z1 > 0]; also the row's squared error.
-__global__ void __launch_bounds__(256) k_mlp_bwd_rows(const float *__restrict__ Y, const float *__restrict__ T,
-                                                      int64_t B, const float *__restrict__ P,
-                                                      const float *__restrict__ Z1, const float *__restrict__ Z2,
-                                                      float *__restrict__ DY, float *__restrict__ DZ1,
-                                                      float *__restrict__ DZ2, float *__restrict__ SE) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= B) return;
-  const float d = Y[r] - T[r];
-  SE[r] = d * d;
-  const float dy = 2.0f * d / (float)B;
-  DY[r] = dy;
-  float dz2[H2];
-  for (int j = 0; j < H2; ++j) {
-    dz2[j] = Z2[r * H2 + j] > 0.0f ? dy * P[O_W3 + j] : 0.0f;
-    DZ2[r * H2 + j] = dz2[j];
-  }
-  for (int k = 0; k < H1; ++k) {
-    float s = 0.0f;
-    for (int j = 0; j < H2; ++j) s = __builtin_fmaf(dz2[j], P[O_W2 + j * H1 + k], s);
-    DZ1[r * H1 + k] = Z1[r * H1 + k] > 0.0f ? s : 0.0f;
+// z[q] = fma(w(k), rows[q][k], z[q]) over k in order, rows in LDS. The reads of
+// the next eight k are under way while these eight are used; the fences keep
+// the compiler from reading one value at a time, or all of them first.
+template <int N, class W>
+__device__ __forceinline__ void mlp_dot(const float (*rows)[N], float (&z)[MLP_R], W &&w) {
+  f32x4m v[2][MLP_R][2];
+  float wv[2][8];
+  auto load = [&](int b, int k) {
+#pragma unroll
+    for (int q = 0; q < MLP_R; ++q) {
+      v[b][q][0] = *(const f32x4m *)&rows[q][k];
+      v[b][q][1] = *(const f32x4m *)&rows[q][k + 4];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) wv[b][e] = w(k + e);
+  };
+  load(0, 0);
+#pragma unroll
+  for (int k = 0; k < N; k += 8) {
+    const int b = (k / 8) & 1;
+    if (k + 8 < N) load(b ^ 1, k + 8);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int q = 0; q < MLP_R; ++q) z[q] = __builtin_fmaf(wv[b][e], v[b][q][e / 4][e % 4], z[q]);
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// One thread per parameter (+1 for the loss): sums its gradient over the
-// batch rows in row order.
-__global__ void __launch_bounds__(256) k_mlp_grad(const float *__restrict__ X, int64_t B, const float *__restrict__ Z1,
-                                                  const float *__restrict__ Z2, const float *__restrict__ DY,
-                                                  const float *__restrict__ DZ1, const float *__restrict__ DZ2,
-                                                  const float *__restrict__ SE, float *__restrict__ G,
-                                                  float *__restrict__ loss) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p > NP) return;
+// Sum over the 64 lanes of a workgroup that is one wavefront, in every lane.
+__device__ __forceinline__ float mlp_sum(float v) {
+  v += dpp_move<0xB1, 0xF>(v, 0.0f);
+  v += dpp_move<0x4E, 0xF>(v, 0.0f);
+  v += dpp_move<0x141, 0xF>(v, 0.0f);
+  v += dpp_move<0x140, 0xF>(v, 0.0f);
+  v += dpp_move<0x142, 0xA>(v, 0.0f);
+  v += dpp_move<0x143, 0xC>(v, 0.0f);
+  return read_lane63(v);
+}
+
+template <bool TRAIN, bool IDX>
+__global__ void __launch_bounds__(64) k_mlp_rows(const float *__restrict__ X, const float *__restrict__ T,
+                                                 const int32_t *__restrict__ idx, int64_t n,
+                                                 const float *__restrict__ P, float *__restrict__ Y,
+                                                 float *__restrict__ part) {
+  __shared__ __attribute__((aligned(16))) float sx[MLP_R][F], sh[MLP_R][H1], sd[TRAIN ? MLP_R : 1][H2], s1[TRAIN ? MLP_R : 1][H1],
+      sw[TRAIN ? H2 : 1][H1];  // W2, for its columns
+  const int j = threadIdx.x, half = j >> 5, l32 = j & 31;
+  float w1[F], w2[H1];
+#pragma unroll
+  for (int k = 0; k < F; k += 4) {
+    const f32x4m v = *(const f32x4m *)(P + O_W1 + j * F + k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w1[k + e] = v[e];
+  }
+#pragma unroll
+  for (int k = 0; k < H1; k += 4) {
+    const f32x4m v = *(const f32x4m *)(P + O_W2 + j * H1 + k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w2[k + e] = v[e];
+  }
+  if constexpr (TRAIN) {
+#pragma unroll
+    for (int k = 0; k < H2; ++k) sw[k][j] = P[O_W2 + k * H1 + j];
+  }
+  const float b1 = P[O_B1 + j], b2 = P[O_B2 + j], w3 = P[O_W3 + j], b3 = P[O_B3];
+  f32x16m g1[TRAIN ? 2 : 1] = {}, g2[TRAIN ? 2 : 1][TRAIN ? 2 : 1] = {};  // W1: 64 x 32, W2: 64 x 64, in 32 x 32 blocks
+  // matrix operands: lane l holds element l mod 32 of row l / 32
+  float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, se = 0.0f;
+  // rows r0 .. r0 + MLP_R - 1 of the next iteration are loaded while this
+  // one's are computed: lane l holds element l mod 32 of row 2 s + l / 32,
+  // and the target of row l mod MLP_R. Past the end: the last row again, not
+  // counted.
+  float xv[MLP_R / 2], tv = 0.0f;
+  auto fetch = [&](int64_t r0, float (&xn)[MLP_R / 2], float &tn) {
+    auto row = [&](int64_t r) {
+      r = r < n ? r : n - 1;
+      return IDX ? (int64_t)idx[r] : r;
+    };
+#pragma unroll
+    for (int s = 0; s < MLP_R / 2; ++s) xn[s] = X[row(r0 + 2 * s + half) * F + l32];
+    if constexpr (TRAIN) tn = T[row(r0 + j % MLP_R)];
+  };
+  fetch((int64_t)blockIdx.x * MLP_R, xv, tv);
+  for (int64_t r0 = (int64_t)blockIdx.x * MLP_R; r0 < n; r0 += (int64_t)gridDim.x * MLP_R) {
+    float z1[MLP_R], z2[MLP_R], xn[MLP_R / 2], tn = 0.0f;
+    __syncthreads();  // the previous rows' readers are done
+#pragma unroll
+    for (int s = 0; s < MLP_R / 2; ++s) sx[2 * s + half][l32] = xv[s];
+    fetch(r0 + (int64_t)gridDim.x * MLP_R, xn, tn);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < MLP_R; ++q) z1[q] = b1;
+    mlp_dot<F>(sx, z1, [&](int k) { return w1[k]; });
+#pragma unroll
+    for (int q = 0; q < MLP_R; ++q) {
+      sh[q][j] = z1[q] > 0.0f ? z1[q] : 0.0f;
+      z2[q] = b2;
+    }
+    __syncthreads();
+    mlp_dot<H1>(sh, z2, [&](int k) { return w2[k]; });
+#pragma unroll
+    for (int q = 0; q < MLP_R; ++q) {
+      const float h2 = z2[q] > 0.0f ? z2[q] : 0.0f;
+      const float y = b3 + mlp_sum(w3 * h2);
+      const bool live = r0 + q < n;
+      if constexpr (!TRAIN) {
+        if (live && j == 0) Y[r0 + q] = y;
+      } else {
+        const float d = live ? y - __shfl(tv, q) : 0.0f, dy = 2.0f * d / (float)n;
+        se += d * d;
+        gb3 += dy;
+        gw3 = __builtin_fmaf(dy, h2, gw3);
+        z2[q] = z2[q] > 0.0f ? dy * w3 : 0.0f;  // the second layer's delta from here on
+        gb2 += z2[q];
+        sd[q][j] = z2[q];
+      }
+    }
+    if constexpr (TRAIN) {
+      __syncthreads();
+      float d1[MLP_R] = {};
+      mlp_dot<H2>(sd, d1, [&](int k) { return sw[k][j]; });
+#pragma unroll
+      for (int q = 0; q < MLP_R; ++q) {
+        if (!(z1[q] > 0.0f)) d1[q] = 0.0f;
+        gb1 += d1[q];
+        s1[q][j] = d1[q];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < MLP_R / 2; ++s)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float a2 = sd[2 * s + half][32 * i + l32], a1 = s1[2 * s + half][32 * i + l32];
+#pragma unroll
+          for (int c = 0; c < 2; ++c)
+            g2[i][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2, sh[2 * s + half][32 * c + l32], g2[i][c], 0, 0, 0);
+          g1[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, xv[s], g1[i], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < MLP_R / 2; ++s) xv[s] = xn[s];
+    tv = tn;
+  }
+  if constexpr (TRAIN) {
+    float *g = part + (int64_t)blockIdx.x * MLP_PART;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int u = 32 * i + 8 * (r / 4) + 4 * half + (r % 4);  // the unit whose weights these are
+        g[O_W1 + u * F + l32] = g1[i][r];
+        g[O_W2 + u * H1 + l32] = g2[i][0][r];
+        g[O_W2 + u * H1 + 32 + l32] = g2[i][1][r];
+      }
+    g[O_B1 + j] = gb1;
+    g[O_B2 + j] = gb2;
+    g[O_W3 + j] = gw3;
+    if (j == 0) {
+      g[O_B3] = gb3;
+      g[NP] = se;
+    }
+  }
+}
+
+// Sums the wavefronts' gradients in order (eight runs of every eighth, then
+// the eight), writes them and the loss, and applies Adam with bias correction
+// (Kingma & Ba 2015) when `adam`. 64 parameters per workgroup, eight threads
+// each.
+__global__ void __launch_bounds__(512) k_mlp_update(const float *__restrict__ part, int nw, int64_t n,
+                                                    float *__restrict__ P, float *__restrict__ G,
+                                                    float *__restrict__ loss, float *__restrict__ M,
+                                                    float *__restrict__ V, bool adam, float lr, float b1, float b2,
+                                                    float eps, float c1, float c2) {
+  __shared__ float s8[8][64];
+  const int t = threadIdx.x % 64, run = threadIdx.x / 64, p = blockIdx.x * 64 + t;
   float s = 0.0f;
+  if (p <= NP) {
+    constexpr int UN = 8;
+    int w = run;
+    for (; w + 8 * (UN - 1) < nw; w += 8 * UN) {
+      float v[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) v[u] = part[(int64_t)(w + 8 * u) * MLP_PART + p];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) s += v[u];
+    }
+    for (; w < nw; w += 8) s += part[(int64_t)w * MLP_PART + p];
+  }
+  s8[run][t] = s;
+  __syncthreads();
+  if (run != 0 || p > NP) return;
+  float g = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) g += s8[q][t];
   if (p == NP) {
-    for (int64_t r = 0; r < B; ++r) s += SE[r];
-    *loss = s / (float)B;
+    *loss = g / (float)n;
     return;
   }
-  if (p < O_B1) {  // W1[j][k] = sum_r dz1[r][j] x[r][k]
-    const int j = p / F, k = p % F;
-    for (int64_t r = 0; r < B; ++r) s = __builtin_fmaf(DZ1[r * H1 + j], X[r * F + k], s);
-  } else if (p < O_W2) {
-    const int j = p - O_B1;
-    for (int64_t r = 0; r < B; ++r) s += DZ1[r * H1 + j];
-  } else if (p < O_B2) {  // W2[j][k] = sum_r dz2[r][j] h1[r][k]
-    const int q = p - O_W2, j = q / H1, k = q % H1;
-    for (int64_t r = 0; r < B; ++r) {
-      const float z = Z1[r * H1 + k];
-      s = __builtin_fmaf(DZ2[r * H2 + j], z > 0.0f ? z : 0.0f, s);
-    }
-  } else if (p < O_W3) {
-    const int j = p - O_B2;
-    for (int64_t r = 0; r < B; ++r) s += DZ2[r * H2 + j];
-  } else if (p < O_B3) {  // W3[j] = sum_r dy[r] h2[r][j]
-    const int j = p - O_W3;
-    for (int64_t r = 0; r < B; ++r) {
-      const float z = Z2[r * H2 + j];
-      s = __builtin_fmaf(DY[r], z > 0.0f ? z : 0.0f, s);
-    }
-  } else {
-    for (int64_t r = 0; r < B; ++r) s += DY[r];
-  }
-  G[p] = s;
-}
-
-// Adam with bias correction (Kingma & Ba 2015).
-__global__ void __launch_bounds__(256) k_adam(float *__restrict__ P, const float *__restrict__ G, float *__restrict__ M,
-                                              float *__restrict__ V, float lr, float b1, float b2, float eps, float c1,
-                                              float c2) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NP) return;
-  const float g = G[p];
+  G[p] = g;
+  if (!adam) return;
   const float m = b1 * M[p] + (1.0f - b1) * g;
   const float v = b2 * V[p] + (1.0f - b2) * g * g;
   M[p] = m;
   V[p] = v;
   const float mh = m / c1, vh = v / c2;
   P[p] = P[p] - lr * mh / (sqrtf(vh) + eps);
-}
-
-// Row gather for minibatches: dst[i] = src[idx[i]] (rows of `w` floats).
-__global__ void k_gather(const float *__restrict__ src, const int32_t *__restrict__ idx, int64_t n, int w,
-                         float *__restrict__ dst) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n * w) return;
-  const int64_t i = e / w, k = e % w;
-  dst[e] = src[(int64_t)idx[i] * w + k];
 }
 
 uint64_t mix64(uint64_t z) {  // SplitMix64 finalizer (Steele, Lea, Flood 2014)
@@ -167,17 +281,15 @@ struct ModelState {
   int64_t step = 0;
   uint64_t seed = 0;
   int64_t epochs = 0;
-  // work buffers for batches of up to `cap` rows
-  int64_t cap = 0;
-  float *X = nullptr, *T = nullptr, *Y = nullptr, *Z1 = nullptr, *Z2 = nullptr, *DY = nullptr, *DZ1 = nullptr,
-        *DZ2 = nullptr, *SE = nullptr, *loss = nullptr;
+  int64_t cap = 0;        // wavefronts `part` has room for
+  float *part = nullptr;  // their gradients
+  float *loss = nullptr;
 };
 
 void upir_model_free(upir_ctx *c) {
   ModelState *m = c->model;
   if (!m) return;
-  for (float *p : {m->P, m->M, m->V, m->G, m->X, m->T, m->Y, m->Z1, m->Z2, m->DY, m->DZ1, m->DZ2, m->SE, m->loss})
-    upir_dfree(c, p);
+  for (float *p : {m->P, m->M, m->V, m->G, m->part, m->loss}) upir_dfree(c, p);
   delete m;
   c->model = nullptr;
 }
@@ -188,26 +300,16 @@ void upir_model_free(upir_ctx *c) {
     if (e_ != hipSuccess) return upir_hipfail(c, e_, #expr); \
   } while (0)
 
-static upir_status model_buffers(upir_ctx *c, int64_t rows) {
+// Gradient room for the `waves` wavefronts of a training step.
+static upir_status model_buffers(upir_ctx *c, int64_t waves) {
   ModelState *m = c->model;
-  if (rows <= m->cap) return UPIR_OK;
-  for (float **p : {&m->X, &m->T, &m->Y, &m->Z1, &m->Z2, &m->DY, &m->DZ1, &m->DZ2, &m->SE}) {
-    upir_dfree(c, *p);
-    *p = nullptr;
-  }
-  const size_t r = (size_t)rows;
-  m->X = (float *)upir_dalloc(c, r * F * 4);
-  m->T = (float *)upir_dalloc(c, r * 4);
-  m->Y = (float *)upir_dalloc(c, r * 4);
-  m->Z1 = (float *)upir_dalloc(c, r * H1 * 4);
-  m->Z2 = (float *)upir_dalloc(c, r * H2 * 4);
-  m->DY = (float *)upir_dalloc(c, r * 4);
-  m->DZ1 = (float *)upir_dalloc(c, r * H1 * 4);
-  m->DZ2 = (float *)upir_dalloc(c, r * H2 * 4);
-  m->SE = (float *)upir_dalloc(c, r * 4);
-  if (!m->X || !m->T || !m->Y || !m->Z1 || !m->Z2 || !m->DY || !m->DZ1 || !m->DZ2 || !m->SE)
-    return upir_fail(c, UPIR_ENOMEM, "model work buffers");
-  m->cap = rows;
+  if (waves <= m->cap) return UPIR_OK;
+  float *np = (float *)upir_dalloc(c, (size_t)waves * MLP_PART * 4);
+  if (!np) return upir_fail(c, UPIR_ENOMEM, "model work buffers");
+  HIPTRY(c, hipStreamSynchronize(c->stream));  // earlier steps may still use the old one
+  upir_dfree(c, m->part);
+  m->part = np;
+  m->cap = waves;
   return UPIR_OK;
 }
 
@@ -277,10 +379,13 @@ extern "C" upir_status upir_model_get_params(upir_ctx *c, float *host) {
   return UPIR_OK;
 }
 
-static hipError_t fwd_launch(upir_ctx *c, const float *X, int64_t n, float *Y, float *Z1, float *Z2) {
+// Predictions of rows idx[0 .. n) of X (idx == nullptr: rows 0 .. n).
+static hipError_t fwd_launch(upir_ctx *c, const float *X, const int32_t *idx, int64_t n, float *Y) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_mlp_fwd, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, X, n, c->model->P, Y, Z1,
-                     Z2);
+  // four wavefronts per SIMD at most: each brings the weights into its registers
+  const int64_t waves = std::min<int64_t>((n + MLP_R - 1) / MLP_R, 16LL * c->num_cus);
+  hipLaunchKernelGGL((idx ? k_mlp_rows<false, true> : k_mlp_rows<false, false>), dim3((unsigned)waves), dim3(64), 0, c->stream, X, (const float *)nullptr, idx,
+                     n, c->model->P, Y, (float *)nullptr);
   return hipGetLastError();
 }
 
@@ -289,32 +394,32 @@ extern "C" upir_status upir_model_forward(upir_ctx *c, const float *dev_x, int64
   upir_status st = need_model(c);
   if (st) return st;
   if (n < 0 || (n > 0 && (!dev_x || !dev_y))) return upir_fail(c, UPIR_EINVAL, "model_forward arguments");
-  HIPTRY(c, fwd_launch(c, dev_x, n, dev_y, nullptr, nullptr));
+  HIPTRY(c, fwd_launch(c, dev_x, nullptr, n, dev_y));
   return UPIR_OK;
 }
 
-// One optimisation step on rows already on the device (X: n x 32, T: n).
-static upir_status step_dev(upir_ctx *c, const float *X, const float *T, int64_t n, float lr, bool adam,
-                            float *grad_out, float *loss_out) {
+// One optimisation step on rows idx[0 .. n) (nullptr: 0 .. n) of X (rows of
+// 32) and T, all on the device.
+static upir_status step_dev(upir_ctx *c, const float *X, const float *T, const int32_t *idx, int64_t n, float lr,
+                            bool adam, float *grad_out, float *loss_out) {
   ModelState *m = c->model;
-  upir_status st = model_buffers(c, n);
+  // every wavefront leaves 25 KB to be summed: from 1,024 rows on they take more
+  // rows each (2,048 rows: 22.5 us with 256 of them, 23.8 with 512), from
+  // 4,096 on the rows weigh more (8,192: 56 against 41 us)
+  const int64_t waves = std::min<int64_t>((n + MLP_R - 1) / MLP_R, n > 4096 ? MLP_WAVES : MLP_WAVES / 2);
+  upir_status st = model_buffers(c, waves);
   if (st) return st;
-  HIPTRY(c, fwd_launch(c, X, n, m->Y, m->Z1, m->Z2));
-  const unsigned g = (unsigned)((n + 255) / 256);
-  hipLaunchKernelGGL(k_mlp_bwd_rows, dim3(g), dim3(256), 0, c->stream, m->Y, T, n, m->P, m->Z1, m->Z2, m->DY, m->DZ1,
-                     m->DZ2, m->SE);
-  hipLaunchKernelGGL(k_mlp_grad, dim3((NP + 1 + 255) / 256), dim3(256), 0, c->stream, X, n, m->Z1, m->Z2, m->DY,
-                     m->DZ1, m->DZ2, m->SE, m->G, m->loss);
-  HIPTRY(c, hipGetLastError());
-  if (grad_out) HIPTRY(c, hipMemcpyAsync(grad_out, m->G, NP * 4, hipMemcpyDeviceToDevice, c->stream));
+  hipLaunchKernelGGL((idx ? k_mlp_rows<true, true> : k_mlp_rows<true, false>), dim3((unsigned)waves), dim3(64), 0, c->stream, X, T, idx, n, m->P,
+                     (float *)nullptr, m->part);
+  float c1 = 1.0f, c2 = 1.0f;
   if (adam) {
     m->step++;
-    const float b1 = 0.9f, b2 = 0.999f;
-    const float c1 = (float)(1.0 - pow(0.9, (double)m->step)), c2 = (float)(1.0 - pow(0.999, (double)m->step));
-    hipLaunchKernelGGL(k_adam, dim3((NP + 255) / 256), dim3(256), 0, c->stream, m->P, m->G, m->M, m->V, lr, b1, b2,
-                       1e-8f, c1, c2);
-    HIPTRY(c, hipGetLastError());
+    c1 = (float)(1.0 - pow(0.9, (double)m->step));
+    c2 = (float)(1.0 - pow(0.999, (double)m->step));
   }
+  hipLaunchKernelGGL(k_mlp_update, dim3((NP + 1 + 63) / 64), dim3(512), 0, c->stream, m->part, (int)waves, n, m->P,
+                     grad_out ? grad_out : m->G, m->loss, m->M, m->V, adam, lr, 0.9f, 0.999f, 1e-8f, c1, c2);
+  HIPTRY(c, hipGetLastError());
   if (loss_out) {
     HIPTRY(c, hipMemcpyAsync(loss_out, m->loss, 4, hipMemcpyDeviceToHost, c->stream));
     HIPTRY(c, hipStreamSynchronize(c->stream));
@@ -328,7 +433,7 @@ extern "C" upir_status upir_model_step(upir_ctx *c, const float *dev_x, const fl
   upir_status st = need_model(c);
   if (st) return st;
   if (n <= 0 || !dev_x || !dev_t) return upir_fail(c, UPIR_EINVAL, "model_step arguments");
-  return step_dev(c, dev_x, dev_t, n, lr, adam != 0, dev_grad, loss_out);
+  return step_dev(c, dev_x, dev_t, nullptr, n, lr, adam != 0, dev_grad, loss_out);
 }
 
 // ------------------------------------------------------------ timing table
@@ -418,15 +523,12 @@ extern "C" upir_status upir_model_train(upir_ctx *c, int32_t epochs, int32_t bat
   }
   float *dX = (float *)upir_dalloc(c, nrow * F * 4), *dT = (float *)upir_dalloc(c, nrow * 4);
   int32_t *dIdx = (int32_t *)upir_dalloc(c, std::max(train.size(), hold.size()) * 4);
-  float *bX = (float *)upir_dalloc(c, (size_t)batch * F * 4), *bT = (float *)upir_dalloc(c, (size_t)batch * 4);
   auto cleanup = [&]() {
     upir_dfree(c, dX);
     upir_dfree(c, dT);
     upir_dfree(c, dIdx);
-    upir_dfree(c, bX);
-    upir_dfree(c, bT);
   };
-  if (!dX || !dT || !dIdx || !bX || !bT) {
+  if (!dX || !dT || !dIdx) {
     cleanup();
     return upir_fail(c, UPIR_ENOMEM, "training buffers");
   }
@@ -450,11 +552,7 @@ extern "C" upir_status upir_model_train(upir_ctx *c, int32_t epochs, int32_t bat
     }
     for (size_t b0 = 0; b0 < order.size(); b0 += batch) {
       const int64_t nb = (int64_t)std::min<size_t>(batch, order.size() - b0);
-      hipLaunchKernelGGL(k_gather, dim3((unsigned)((nb * F + 255) / 256)), dim3(256), 0, c->stream, dX, dIdx + b0, nb,
-                         F, bX);
-      hipLaunchKernelGGL(k_gather, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, c->stream, dT, dIdx + b0, nb, 1,
-                         bT);
-      st = step_dev(c, bX, bT, nb, lr, true, nullptr, nullptr);
+      st = step_dev(c, dX, dT, dIdx + b0, nb, lr, true, nullptr, nullptr);
       if (st) break;
     }
     // keep the index buffer alive until this epoch's kernels have read it
@@ -470,23 +568,18 @@ extern "C" upir_status upir_model_train(upir_ctx *c, int32_t epochs, int32_t bat
       return UPIR_OK;
     }
     float *dY = (float *)upir_dalloc(c, rows.size() * 4);
-    float *gX = (float *)upir_dalloc(c, rows.size() * F * 4);
-    if (!dY || !gX) {
-      upir_dfree(c, dY);
-      upir_dfree(c, gX);
+    if (!dY) {
       return upir_fail(c, UPIR_ENOMEM, "evaluation buffers");
     }
     hipError_t e2 = hipMemcpyAsync(dIdx, rows.data(), rows.size() * 4, hipMemcpyHostToDevice, c->stream);
     const int64_t n = (int64_t)rows.size();
     if (e2 == hipSuccess) {
-      hipLaunchKernelGGL(k_gather, dim3((unsigned)((n * F + 255) / 256)), dim3(256), 0, c->stream, dX, dIdx, n, F, gX);
-      e2 = fwd_launch(c, gX, n, dY, nullptr, nullptr);
+      e2 = fwd_launch(c, dX, dIdx, n, dY);
     }
     std::vector<float> y(n);
     if (e2 == hipSuccess) e2 = hipMemcpyAsync(y.data(), dY, n * 4, hipMemcpyDeviceToHost, c->stream);
     if (e2 == hipSuccess) e2 = hipStreamSynchronize(c->stream);
     upir_dfree(c, dY);
-    upir_dfree(c, gX);
     if (e2 != hipSuccess) return upir_hipfail(c, e2, "evaluation");
     double s = 0;
     for (int64_t i = 0; i < n; ++i) {
@@ -729,7 +822,7 @@ bool model_pick(upir_ctx *c, upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc) {
   std::vector<float> y(cs.size());
   bool ok = dX && dY;
   if (ok) ok = hipMemcpyAsync(dX, X.data(), X.size() * 4, hipMemcpyHostToDevice, c->stream) == hipSuccess;
-  if (ok) ok = fwd_launch(c, dX, (int64_t)cs.size(), dY, nullptr, nullptr) == hipSuccess;
+  if (ok) ok = fwd_launch(c, dX, nullptr, (int64_t)cs.size(), dY) == hipSuccess;
   if (ok) ok = hipMemcpyAsync(y.data(), dY, y.size() * 4, hipMemcpyDeviceToHost, c->stream) == hipSuccess;
   if (ok) ok = hipStreamSynchronize(c->stream) == hipSuccess;
   upir_dfree(c, dX);
@@ -863,7 +956,7 @@ bool model_pick_engine(upir_ctx *c, upir_engine_sched &es) {
   float *dX = (float *)upir_dalloc(c, X.size() * 4), *dY = (float *)upir_dalloc(c, cs.size() * 4);
   bool ok = dX && dY;
   if (ok) ok = hipMemcpyAsync(dX, X.data(), X.size() * 4, hipMemcpyHostToDevice, c->stream) == hipSuccess;
-  if (ok) ok = fwd_launch(c, dX, (int64_t)cs.size(), dY, nullptr, nullptr) == hipSuccess;
+  if (ok) ok = fwd_launch(c, dX, nullptr, (int64_t)cs.size(), dY) == hipSuccess;
   if (ok) ok = hipMemcpyAsync(y.data(), dY, y.size() * 4, hipMemcpyDeviceToHost, c->stream) == hipSuccess;
   if (ok) ok = hipStreamSynchronize(c->stream) == hipSuccess;
   upir_dfree(c, dX);
