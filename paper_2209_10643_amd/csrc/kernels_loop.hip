@@ -420,15 +420,18 @@ hipError_t launch_stream4(int32_t body, const void *payload, const LoopK &L, con
 // LDS, so no barrier separates loads from arithmetic.
 constexpr int JT_W = 256;  // tile width (points)
 
-// Residual reduction per lane. The float64 value of |u1 - u0| is only needed
-// where it can change the lane's maximum (or minimum): rounding to float32
-// is monotonic, so a point whose float32 |u1 - u0| is below the lane's
-// float32 maximum cannot hold the exact maximum. Only candidates at or above
-// it take the float64 path, and a row of four points where none is a
-// candidate costs one comparison; the result is exact.
+// Residual reduction. The float64 value of |u1 - u0| is only needed where it
+// can change the maximum (or minimum): rounding to float32 is monotonic, so a
+// point whose float32 |u1 - u0| is below a maximum already found cannot hold
+// the exact one. The threshold is the wavefront's, over all its lanes: a row
+// of 256 points passes the r - 1 rows before it with chance 1 / r, so a strip
+// of sixteen rows takes the float64 path about three times. (With a threshold
+// per lane some lane of the 64 passed its own in nearly every row.) Only
+// candidates at or above it take that path; the result is exact.
 template <int OP>
 struct ResidualAcc {
-  float m32 = OP == RED_MIN ? __builtin_inff() : -1.0f;
+  float m32 = OP == RED_MIN ? __builtin_inff() : -1.0f;  // this lane's best candidate, in float32
+  float w32 = m32;                                       // the wavefront's
   double m64 = OP == RED_SUM ? 0.0 : (OP == RED_MAX ? -__builtin_inf() : __builtin_inf());
   __device__ void add(float v, float c) {
     if (OP == RED_SUM) {
@@ -446,20 +449,35 @@ struct ResidualAcc {
       }
     }
   }
+  template <int CTRL, int RM>
+  __device__ static float best(float v) {
+    const float o = dpp_move<CTRL, RM>(v, v);
+    return OP == RED_MAX ? fmaxf(v, o) : fminf(v, o);
+  }
   // The four points of a lane's row; bit e of `mk` marks point e as in the
-  // loop box.
+  // loop box. Every lane of the wavefront calls it.
   __device__ void add4(const f32x4 &v, const f32x4 &c, int mk) {
     if (OP != RED_SUM) {
       constexpr float NONE = OP == RED_MAX ? -1.0f : __builtin_inff();
       const float d0 = mk & 1 ? fabsf(v.x - c.x) : NONE, d1 = mk & 2 ? fabsf(v.y - c.y) : NONE;
       const float d2 = mk & 4 ? fabsf(v.z - c.z) : NONE, d3 = mk & 8 ? fabsf(v.w - c.w) : NONE;
       const float dm = OP == RED_MAX ? fmaxf(fmaxf(d0, d1), fmaxf(d2, d3)) : fminf(fminf(d0, d1), fminf(d2, d3));
-      if (OP == RED_MAX ? dm < m32 : dm > m32) return;
+      if (__builtin_amdgcn_ballot_w64(OP == RED_MAX ? dm >= w32 : dm <= w32) == 0) return;
     }
     if (mk & 1) add(v.x, c.x);
     if (mk & 2) add(v.y, c.y);
     if (mk & 4) add(v.z, c.z);
     if (mk & 8) add(v.w, c.w);
+    if (OP != RED_SUM) {  // the wavefront's best, by the steps of its reduction tree
+      float w = m32;
+      w = best<0xB1, 0xF>(w);
+      w = best<0x4E, 0xF>(w);
+      w = best<0x141, 0xF>(w);
+      w = best<0x140, 0xF>(w);
+      w = best<0x142, 0xA>(w);
+      w = best<0x143, 0xC>(w);
+      w32 = read_lane63(w);
+    }
   }
 };
 
@@ -586,19 +604,19 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   const int TH = S.tile[0];
   const int lane = threadIdx.x % WAVE;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), NW = blockDim.x / WAVE;
-  // The launch's cross-workgroup work goes to one extra workgroup, launched
-  // last and given no tile, so that its latency hides behind the tiles still
-  // running: the fold of an earlier loop's deferred reduction, and the
-  // combine of this loop's own synchronous reduction (as the last-launched
-  // workgroup it is the combiner; its own value is the identity).
-  const bool xwg = jacobi_extra_wg(R);
-  const int G = xwg ? gridDim.x - 1 : gridDim.x;
-  if (xwg && (int)blockIdx.x == G) {
+  // The launch's cross-workgroup work goes to one extra workgroup that is
+  // given no tile. The combine of this loop's own synchronous reduction waits
+  // for every other workgroup and must be launched last; the fold of an
+  // earlier loop's deferred reduction waits for none and is launched first,
+  // so that it runs beside the tiles however many rounds of them there are.
+  const bool xwg = jacobi_extra_wg(R), combine = RED && !R.defer, first = xwg && !combine;
+  const int G = xwg ? gridDim.x - 1 : gridDim.x, wg = (int)blockIdx.x - (first ? 1 : 0);
+  if (xwg && wg == (first ? -1 : G)) {
     if (R.fold.count > 0) run_fold(R.fold);
-    if (RED && !R.defer) finish_reduction<double>(R, ResidualAcc<RED>().m64);
+    if (combine) finish_reduction<double>(R, ResidualAcc<RED>().m64);
     return;
   }
-  const int team = xcd_team(blockIdx.x, G);
+  const int team = xcd_team(wg, G);
   const int SH = (TH + NW - 1) / NW;                          // strip height
   const int64_t ilo = L.lb[0], ihi = L.lb[0] + L.cnt[0];  // interior rows [ilo, ihi)
   const int64_t jlo = L.lb[1], jhi = L.lb[1] + L.cnt[1];
@@ -632,7 +650,10 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
     for (int64_t m0 = (int64_t)team * c; m0 < S.ntiles; m0 += (int64_t)S.T * c)
       for (int64_t m = m0; m < m0 + c && m < S.ntiles; ++m) do_tile(m);
   }
-  if (RED) finish_reduction<double>(R, acc.m64);
+  if (RED) {
+    if (R.defer) defer_partial<double>(R, acc.m64, wg);
+    else finish_reduction<double>(R, acc.m64);
+  }
 }
 
 // The schedules and boxes the strips run, whatever the grid's pitch and
@@ -752,9 +773,9 @@ hipError_t launch_matvec_wave(const MatvecP &p, const LoopK &L, const SchedK &S,
 
 // Standalone fold of a deferred reduction (one workgroup).
 namespace upir {
-__global__ void __launch_bounds__(256) k_fold(FoldK F) { run_fold(F); }
+__global__ void __launch_bounds__(1024) k_fold(FoldK F) { run_fold(F); }
 hipError_t launch_fold(const FoldK &F, hipStream_t st) {
-  hipLaunchKernelGGL(k_fold, dim3(1), dim3(256), 0, st, F);
+  hipLaunchKernelGGL(k_fold, dim3(1), dim3(F.count > 2048 ? 1024 : 256), 0, st, F);
   return hipGetLastError();
 }
 }  // namespace upir

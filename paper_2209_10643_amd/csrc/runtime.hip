@@ -698,14 +698,18 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // rows) that still keeps the device busy. Up to 32 rows 1.5 x CUs tiles
       // are enough (sweeps of 1501 x 2003, maximum taken: 12.5 us with 752
       // tiles of 16 rows, 13.1 with 376 of 32, 14.9 with 1504 of 8; 1000 x
-      // 1001: 9.2 with 500 of 8, 10.9 with 1000 of 4). Without a residual
-      // strips of more than 4 rows only lengthen each wavefront's chain (4096
-      // x 4096: 21.1 us on 16 rows, 23.0 on 64). With one, 64 rows are worth
-      // it where the tiles fill the 4 x CUs resident ones once, or often
-      // enough that the last round does not count (4096 x 4096 24.1 us async
-      // against 24.5 on 32; 4833 x 5992, 1.8 rounds, 40.7 against 38.0), and
-      // 128 where the grids leave the last-level cache (16384 x 16384: 407 us
-      // against 430). The filter brings six more rows per tile into
+      // 1001: 9.2 with 500 of 8, 10.9 with 1000 of 4). Without a residual, or
+      // with one that is folded later, taller strips only lengthen each
+      // wavefront's chain (4096 x 4096 without: 21.1 us on 16 rows, 23.0 on
+      // 64; async: 23.5 and 23.4; 4833 x 5992 async: 36.0, 38.0 on 32, 40.1
+      // on 64; 8192 x 8192: 89 on 16, 98 on 128), until the partials, one per
+      // wavefront, are too many for one workgroup's fold: 32 rows from 64 x
+      // CUs tiles on. A synchronous residual pays for every workgroup (the
+      // last one reads a value from each): 64 rows where the tiles fill the
+      // 4 x CUs resident ones once, or often enough that the last round does
+      // not count (4096 x 4096: 27.9 us, 29.0 on 32; 4833 x 5992, 1.8
+      // rounds, 44.5 against 42.0), and 128 where the grids leave the
+      // last-level cache. The filter brings six more rows per tile into
       // LDS and takes 2 x CUs tiles (1024 x 1024: 6.6 us on 8 rows, 7.4 on 4;
       // 1001 x 1501: 8.0 on 8, 8.7 on 16, 10.3 on 4), 32 rows from 4 x CUs
       // tiles on (2048 x 2048: 12.2 us on 16, 12.4 on 32; 8192 x 8192: 136 on
@@ -719,7 +723,10 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       auto enough = [&](int th) {
         const int64_t tiles = cdiv(rows, th) * ct;
         if (filter) return th <= 32 && tiles >= (th == 32 ? 4 : 2) * cus;
-        if (th > 16 && !lp->has_red) return false;
+        if (!lp->has_red || lp->red.async) {
+          if (th > 32 || (th == 32 && cdiv(rows, 16) * ct <= 64 * cus)) return false;
+          return 2 * tiles >= 3 * cus;
+        }
         if (th == 128) return tiles >= 8 * cus;
         if (th == 64) return (tiles >= 4 * cus && 16 * tiles <= 17 * 4 * cus) || tiles >= 12 * cus;
         return 2 * tiles >= 3 * cus;
@@ -1000,7 +1007,9 @@ upir_status settle(upir_ctx *c) {
 static upir_status ensure_fold_bufs(upir_ctx *c, int64_t parts) {
   if (parts <= c->fold_cap) return UPIR_OK;
   if (c->capturing) return upir_fail(c, UPIR_ESTATE, "fold buffers must grow; launch once before capturing");
-  const int64_t cap = std::max<int64_t>(parts, 1 << 16);
+  // room for every default launch up to grids of 32768 x 32768, so that a
+  // capture finds it whatever async loop ran first
+  const int64_t cap = std::max<int64_t>(parts, 1 << 20);
   unsigned long long *nb[2];
   for (int i = 0; i < 2; ++i) {
     nb[i] = (unsigned long long *)upir_dalloc(c, (size_t)cap * 8);

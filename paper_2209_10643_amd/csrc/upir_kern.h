@@ -447,14 +447,14 @@ __device__ inline void combine_i64(const RedK &R, long long wg, long long *lds) 
 // defer[workgroup * wavefronts-per-workgroup + wavefront]; no barrier and no
 // cross-workgroup traffic in this kernel.
 template <class T>
-__device__ inline void defer_partial(const RedK &R, T lane) {
+__device__ inline void defer_partial(const RedK &R, T lane, int wg = blockIdx.x) {
   const T w = wave_reduce(R.op, lane);
   if (threadIdx.x % WAVE == 0) {
     const int nw = (blockDim.x + WAVE - 1) / WAVE;
     unsigned long long bits;
     if constexpr (std::is_same<T, long long>::value) bits = (unsigned long long)w;
     else bits = __builtin_bit_cast(unsigned long long, (double)w);
-    R.defer[(long long)blockIdx.x * nw + threadIdx.x / WAVE] = bits;
+    R.defer[(long long)wg * nw + threadIdx.x / WAVE] = bits;
   }
 }
 
