@@ -699,73 +699,122 @@ hipError_t launch_jacobi_tile(const JacobiP &p, const LoopK &L, const SchedK &S,
 // under the schedule with U/64 units per team. Inside a row, lane l takes
 // columns 4l .. 4l+3 of every 256-column block in order, then the 64 lane
 // sums meet in a fixed reduction tree.
-template <bool RED>
-__global__ void __launch_bounds__(1024) k_matvec(LoopK L, SchedK S, MatvecP p, RedK R) {
-  const int lane = threadIdx.x % WAVE, w = threadIdx.x / WAVE;
-  SchedK SW = S;
-  SW.U = S.U / WAVE;
-  float acc = RED ? red_identity<float>(R.op) : 0.0f;
-  const bool vec = (p.lda % 4 == 0) && ((uintptr_t)p.A % 16 == 0) && ((uintptr_t)p.x % 16 == 0);
-  auto row = [&](int64_t, const int64_t *iv) {
-    const int64_t r = iv[0];
-    const float *a = p.A + r * p.lda;
-    float s = 0.0f;
-    int64_t c0 = 0;
-    if (vec) {
-      // eight (then four) 256-column blocks per trip: their loads are all
-      // issued before the multiply-adds, which keep the block-by-block order
-      // (N = 16384: 191 us against 238 us one block at a time)
-      auto blocks = [&](auto nb) {
-        constexpr int NB = decltype(nb)::value;
-        for (; c0 + 256 * NB <= p.cols; c0 += 256 * NB) {
-          f32x4 av[NB], xv[NB];
+//
+// A wavefront works on RW of its rows together (the chunk-1 schedule, where
+// they are a fixed stride apart), so that a vector of x serves RW rows: one
+// row at a time x comes out of the caches as often as A out of memory
+// (16384 x 16384: 185 us; here 154, 7.0 TB/s). The values of a row do not
+// depend on RW. NT: A is streamed past the caches. Rows of any pitch are read
+// 16 bytes per lane (16384 x 1001: 34 to 13 us).
+template <bool NT>
+__device__ __forceinline__ f32x4 mv_ld(const float *p) {
+  if (NT) return __builtin_nontemporal_load((const f32x4u *)p);
+  return *(const f32x4u *)p;
+}
+
+// s[u] += the products of the `cols` columns of row a[u] with x. (Letting the
+// wavefronts of a team share a row took 255 x 39807 from 13.3 to 8.9 us, but
+// changes the order of a row's sum, which the batched executor's rows share.)
+template <int RW, bool NT>
+__device__ __forceinline__ void mv_rows(const float *const (&a)[RW], const float *x, int64_t cols, int lane, float (&s)[RW]) {
+  int64_t c0 = 0;
+  // a few blocks per trip: their loads are all issued before the
+  // multiply-adds, which keep the block-by-block order
+  auto blocks = [&](auto nb) {
+    constexpr int NB = decltype(nb)::value;
+    for (; c0 + NB * 256 <= cols; c0 += NB * 256) {
+      f32x4 av[RW][NB], xv[NB];
 #pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            av[u] = *(const f32x4 *)(a + c0 + 256 * u + 4 * lane);
-            xv[u] = *(const f32x4 *)(p.x + c0 + 256 * u + 4 * lane);
-          }
+      for (int b = 0; b < NB; ++b) {
+        const int64_t c = c0 + b * 256 + 4 * lane;
+        xv[b] = *(const f32x4u *)(x + c);
 #pragma unroll
-          for (int u = 0; u < NB; ++u) {
-            s = __builtin_fmaf(av[u].x, xv[u].x, s);
-            s = __builtin_fmaf(av[u].y, xv[u].y, s);
-            s = __builtin_fmaf(av[u].z, xv[u].z, s);
-            s = __builtin_fmaf(av[u].w, xv[u].w, s);
-          }
-        }
-      };
-      blocks(std::integral_constant<int, 8>{});
-      blocks(std::integral_constant<int, 4>{});
-    }
-    for (; c0 < p.cols; c0 += 256) {
-      const int64_t c = c0 + 4 * lane;
-      if (vec && c + 3 < p.cols) {
-        const f32x4 av = *(const f32x4 *)(a + c);
-        const f32x4 xv = *(const f32x4 *)(p.x + c);
-        s = __builtin_fmaf(av.x, xv.x, s);
-        s = __builtin_fmaf(av.y, xv.y, s);
-        s = __builtin_fmaf(av.z, xv.z, s);
-        s = __builtin_fmaf(av.w, xv.w, s);
-      } else {
-        for (int q = 0; q < 4; ++q)
-          if (c + q < p.cols) s = __builtin_fmaf(a[c + q], p.x[c + q], s);
+        for (int u = 0; u < RW; ++u) av[u][b] = mv_ld<NT>(a[u] + c);
       }
-    }
-    s = wave_reduce(RED_SUM, s);
-    if (lane == 0) {
-      p.y[r] = s;
-      if (RED) acc = red_apply(R.op, acc, s);
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int u = 0; u < RW; ++u)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[u] = __builtin_fmaf(av[u][b][e], xv[b][e], s[u]);
     }
   };
-  for_owned_untiled(L, SW, blockIdx.x, w, row);
+  if constexpr (RW == 1) blocks(std::integral_constant<int, 8>{});
+  blocks(std::integral_constant<int, RW == 4 ? 3 : 4>{});
+  blocks(std::integral_constant<int, 1>{});
+  if (c0 < cols) {  // the last, partial block
+    const int64_t c = c0 + 4 * lane;
+#pragma unroll
+    for (int u = 0; u < RW; ++u) {
+      if (c + 3 < cols) {
+        const f32x4 av = *(const f32x4u *)(a[u] + c), xv = *(const f32x4u *)(x + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[u] = __builtin_fmaf(av[e], xv[e], s[u]);
+      } else {
+        for (int e = 0; e < 4; ++e)
+          if (c + e < cols) s[u] = __builtin_fmaf(a[u][c + e], x[c + e], s[u]);
+      }
+    }
+  }
+}
+
+template <int RW, bool RED, bool NT>
+__global__ void __launch_bounds__(1024) k_matvec(LoopK L, SchedK S, MatvecP p, RedK R) {
+  const int lane = threadIdx.x % WAVE, w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  float acc = RED ? red_identity<float>(R.op) : 0.0f;
+  auto rows = [&](auto rr, int64_t k, int64_t stride) {
+    constexpr int N = decltype(rr)::value;
+    const float *a[N];
+    float s[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      a[u] = p.A + (L.lb[0] + (k + u * stride) * L.step[0]) * p.lda;
+      s[u] = 0.0f;
+    }
+    mv_rows<N, NT>(a, p.x, p.cols, lane, s);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const float y = wave_reduce(RED_SUM, s[u]);
+      if (lane == 0) {
+        p.y[L.lb[0] + (k + u * stride) * L.step[0]] = y;
+        if (RED) acc = red_apply(R.op, acc, y);
+      }
+    }
+  };
+  if constexpr (RW > 1) {  // chunk 1 over teams and waves
+    const int NW = S.U / WAVE;
+    const int64_t stride = (int64_t)S.T * NW;
+    int64_t k = (int64_t)blockIdx.x * NW + w;
+    for (; k + (RW - 1) * stride < L.n; k += RW * stride) rows(std::integral_constant<int, RW>{}, k, stride);
+    for (; k < L.n; k += stride) rows(std::integral_constant<int, 1>{}, k, stride);
+  } else {
+    SchedK SW = S;
+    SW.U = S.U / WAVE;
+    auto row = [&](int64_t k, const int64_t *) { rows(std::integral_constant<int, 1>{}, k, 0); };
+    for_owned_untiled(L, SW, blockIdx.x, w, row);
+  }
   if (RED) finish_reduction<float>(R, acc);
   fold_hook(R);
 }
 
+template <int RW, bool RED>
+static void go_matvec(bool nt, const MatvecP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
+  if (nt) hipLaunchKernelGGL((k_matvec<RW, RED, true>), dim3(S.T), dim3(S.U), 0, st, L, S, p, R);
+  else hipLaunchKernelGGL((k_matvec<RW, RED, false>), dim3(S.T), dim3(S.U), 0, st, L, S, p, R);
+}
+
 hipError_t launch_matvec_wave(const MatvecP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
-  if (R.op != RED_NONE)
-    hipLaunchKernelGGL(k_matvec<true>, dim3(S.T), dim3(S.U), 0, st, L, S, p, R);
-  else
-    hipLaunchKernelGGL(k_matvec<false>, dim3(S.T), dim3(S.U), 0, st, L, S, p, R);
+  const bool nt = (uint64_t)L.n * (uint64_t)p.cols * 4u >= (64ull << 20);  // as for the streams
+  const int64_t waves = (int64_t)S.T * (S.U / WAVE);
+  const bool strided = S.policy == POL_CHUNK && S.chunk == 1 && S.dist == DIST_TU;
+  if (R.op != RED_NONE) {
+    if (strided && L.n >= 4 * waves) go_matvec<4, true>(nt, p, L, S, R, st);
+    else go_matvec<1, true>(nt, p, L, S, R, st);
+  } else {
+    if (strided && L.n >= 4 * waves) go_matvec<4, false>(nt, p, L, S, R, st);
+    else if (strided && L.n >= 2 * waves) go_matvec<2, false>(nt, p, L, S, R, st);
+    else go_matvec<1, false>(nt, p, L, S, R, st);
+  }
   return hipGetLastError();
 }
 

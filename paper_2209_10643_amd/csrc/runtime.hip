@@ -789,11 +789,25 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       }
       break;
     }
-    case UPIR_BODY_MATVEC:
+    case UPIR_BODY_MATVEC: {
+      const int64_t cols = ((const upir_matvec_args *)lp->args)->cols, cus = c->num_cus;
       sc.policy = UPIR_SCHED_STATIC_CHUNK;
       sc.chunk = 1;
-      sp.num_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
+      if (n < 4 * cus && !lp->has_red) {  // a wavefront per row on CUs of their own (255 x 39807:
+        // 13.3 us, 19.2 four to a team; 300 x 5000: 4.9 and 5.9)
+        sp.num_teams = (int32_t)std::max<int64_t>(1, n);
+        sp.num_units = 64;
+      } else if (n * cols >= (128LL << 20) && n >= 8 * cus && !lp->has_red) {
+        // 512 MiB of A and more: eight wavefronts per CU (16384 x 16384: 154
+        // us with 2,048 of them, 181 with 8,192; 4096 x 40000: 100 and 103;
+        // at 5376 x 20972, 430 MiB, 81 and 78)
+        sp.num_teams = (int32_t)cus;
+        sp.num_units = 512;
+      } else {
+        sp.num_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
+      }
       break;
+    }
     default:
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 256), cap));
@@ -905,6 +919,8 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     if (S.tiled) {
       T = S.policy == UPIR_SCHED_STATIC ? S.ntiles : cdiv(S.ntiles, S.chunk);
       if (is_matmul(lp->kind) || lp->kind == UPIR_BODY_JACOBI5 || lp->kind == UPIR_BODY_FILTER7) T = std::max<int64_t>(T, 1);
+    } else if (lp->kind == UPIR_BODY_MATVEC && sp.num_units != dsp.num_units) {
+      T = std::max<int64_t>(1, std::min<int64_t>(cdiv(L.n, 4), 8LL * c->num_cus));  // teams of a size the default is not for
     } else {
       T = dsp.num_teams > 0 ? dsp.num_teams : 1;
     }
