@@ -134,13 +134,14 @@ struct TeamRanges {
   }
 };
 
-template <bool NT, class V>
-__device__ __forceinline__ V ldv(const V *p) {
+// By element type: a deduced vector type would lose its element alignment.
+template <bool NT, class T>
+__device__ __forceinline__ typename Vec16<T>::V ldv(const typename Vec16<T>::V *p) {
   if constexpr (NT) return __builtin_nontemporal_load(p);
   else return *p;
 }
-template <bool NT, class V>
-__device__ __forceinline__ void stv(V *p, V v) {
+template <bool NT, class T>
+__device__ __forceinline__ void stv(typename Vec16<T>::V *p, typename Vec16<T>::V v) {
   if constexpr (NT) __builtin_nontemporal_store(v, p);
   else *p = v;
 }
@@ -166,7 +167,7 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
     if constexpr (AXPY) {
 #pragma unroll
       for (int q = 0; q < W; ++q) yv[q] = __builtin_fmaf(a, xv[q], yv[q]);
-      stv<NT>(out, yv);
+      stv<NT, T>(out, yv);
       if (OP) {
 #pragma unroll
         for (int q = 0; q < W; ++q) acc = red_apply(OP, acc, (A)yv[q]);
@@ -194,8 +195,8 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
       V xb[UN], yb[UN] = {};
 #pragma unroll
       for (int u = 0; u < UN; ++u) {
-        xb[u] = ldv<NT>(&xv[m + u * U]);
-        if constexpr (AXPY) yb[u] = ldv<NT>(&yv[m + u * U]);
+        xb[u] = ldv<NT, T>(&xv[m + u * U]);
+        if constexpr (AXPY) yb[u] = ldv<NT, T>(&yv[m + u * U]);
       }
 #pragma unroll
       for (int u = 0; u < UN; ++u) vec(xb[u], yb[u], yv + m + u * U);
@@ -206,8 +207,8 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
 #pragma unroll
       for (int u = 0; u < UN - 1; ++u)
         if (m + (int64_t)u * U < nv) {
-          xb[u] = ldv<NT>(&xv[m + u * U]);
-          if constexpr (AXPY) yb[u] = ldv<NT>(&yv[m + u * U]);
+          xb[u] = ldv<NT, T>(&xv[m + u * U]);
+          if constexpr (AXPY) yb[u] = ldv<NT, T>(&yv[m + u * U]);
         }
 #pragma unroll
       for (int u = 0; u < UN - 1; ++u)
