@@ -11,10 +11,10 @@
 //    a global work list (one atomic reservation per task); workgroups claim
 //    work items with one global counter and wait, if needed, until the item
 //    they hold has been filled in by the push that reserved it;
-//  * the workgroup that finishes a task's last tile combines the task's
-//    reduction (float64, tile order), writes its trace token and stamps, and
-//    decrements the remaining in-degree of each successor, pushing those
-//    that reach zero;
+//  * a wavefront of the workgroup that finishes a task's last tile combines
+//    the task's reduction (float64, a fixed order), writes its trace token
+//    and stamps, and decrements the remaining in-degree of each successor,
+//    pushing those that reach zero;
 //  * every wait is bounded: a workgroup that sees no progress for a long
 //    time raises an error flag and leaves, so the kernel always drains.
 //
@@ -66,6 +66,14 @@ __device__ inline int ld_i(int32_t *p) { return __hip_atomic_load(p, __ATOMIC_RE
 __device__ inline void st_i(int32_t *p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ inline int add_i(int32_t *p, int v) {
   return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The same, not waited for before its value is used: on an address that it
+// knows to be uniform the compiler adds up the lanes first and reads the
+// result back at once, a round trip through memory in the wave's path.
+__device__ inline int add_i_later(int32_t *p, int v) {
+  int zero = 0;
+  __asm__ volatile("" : "+v"(zero));
+  return add_i(p + zero, v);
 }
 __device__ inline unsigned long long ld_u64(unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -345,10 +353,88 @@ __device__ inline void run_tile(const TaskD &t, int64_t tile, float &acc) {
   }
 }
 
+// A task's descriptor through the scalar cache (it does not change while the
+// engine runs): read with vector loads, every field was one more dependent
+// access before the tile's first load.
+__device__ __forceinline__ TaskD load_task(const TaskD *tasks, int t) {
+  typedef const __attribute__((address_space(4))) uint32_t cword;
+  constexpr int N = sizeof(TaskD) / 4;
+  static_assert(sizeof(TaskD) % 4 == 0, "words");
+  cword *src = (cword *)(tasks + t);
+  uint32_t w[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) w[i] = src[i];
+  TaskD d;
+  __builtin_memcpy(&d, w, sizeof d);
+  return d;
+}
+
+// What a finished task leaves and starts, by one wavefront: the reduction
+// over its tiles, its token and stamp, and its successors, one lane each.
+__device__ __forceinline__ void finish_task(const EngineD &E, const TaskD &d, int t, int lane, double partial) {
+  if (d.red_op) {
+    // the order in which a workgroup of 256 would fold them: lane l of group
+    // u takes tiles 64 u + l, then every 256th; groups fold in order
+    constexpr int NU = 4;
+    const double id = red_identity<double>(d.red_op);
+    double v[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) v[u] = id;
+    if (d.ntiles == 1) {
+      if (lane == 0) v[0] = red_apply(d.red_op, id, partial);
+    } else {
+      for (int i0 = lane; i0 < d.ntiles; i0 += NU * WAVE) {
+        unsigned long long b[NU];
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          b[u] = i0 + u * WAVE < d.ntiles ? coh_load((unsigned long long *)&E.partials[d.part_base + i0 + u * WAVE]) : 0ULL;
+#pragma unroll
+        for (int u = 0; u < NU; ++u)
+          if (i0 + u * WAVE < d.ntiles) v[u] = red_apply(d.red_op, v[u], __builtin_bit_cast(double, b[u]));
+      }
+    }
+    double r = id;
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (u * WAVE < d.ntiles) {
+        const double g = wave_reduce(d.red_op, v[u]);
+        if (lane == u) r = g;
+      }
+    r = wave_reduce(d.red_op, r);
+    if (lane == 0)
+      coh_store((unsigned long long *)d.result, __builtin_bit_cast(unsigned long long, red_apply(d.red_op, d.init, r)));
+  }
+  if (lane == 0) {
+    if (E.tok) {
+      uint64_t hsh = mix64((uint64_t)(t + 1) * 0x9E3779B97F4A7C15ULL);
+      for (int i = d.pred_begin; i < d.pred_end; ++i) hsh = mix64(hsh ^ coh_load((unsigned long long *)&E.tok[E.pred[i]]));
+      coh_store((unsigned long long *)&E.tok[t], hsh);
+    }
+    if (E.tdone) E.tdone[t] = tick(E.clock);
+  }
+  if (d.succ_begin == d.succ_end) return;
+  complete_own_accesses();  // result, token and stamp before any successor starts
+  for (int i = d.succ_begin + lane; i < d.succ_end; i += WAVE) {
+    const int s = E.succ[i], nt = E.tasks[s].ntiles;
+    if (add_i(&E.indeg[s], -1) == 1) {
+      const int base = add_i(&E.ctrl[0], nt);
+      for (int q = 0; q < nt; ++q) st_u64(&E.work[base + q], work_item(s, q));
+    }
+  }
+}
+
+// Where the time of a small graph goes is the chain from a task's last store
+// to its successor's first load. One wavefront finishes a task while the
+// others wait for the next item; a task of one tile needs neither the tile
+// counter nor the partial's way through memory; successors are released by
+// one lane each; and the next item is looked up before the current tile's
+// reduction, not after its end. Graphs of small tasks, before and after: 485
+// tasks of 2^8 .. 2^14 elements 100 -> 69 us, 77 tasks 48 -> 38 us, 600 with
+// four edges each 168 -> 108 us, 1024 of up to 2^20 248 -> 187 us. A graph of
+// 2048 up to 2^22 is bound by HBM: 1027 -> 1003 us for 5.4 GB.
 __global__ void __launch_bounds__(256) k_engine(EngineD E) {
-  __shared__ int s_task, s_tile, s_last;
+  __shared__ int s_task[2], s_tile[2];  // two items: the next is written while slow wavefronts still read this one
   __shared__ float s_red[16];
-  __shared__ double s_red64[16];
   // Work items are dealt round-robin over nq queues, each with its own claim
   // counter (one atomic per claim; a single counter for the whole chip
   // serialised the claims). Workgroup b claims from queue b mod nq, items
@@ -357,91 +443,75 @@ __global__ void __launch_bounds__(256) k_engine(EngineD E) {
   // round trip overlaps the tile's memory traffic. A workgroup finishes its
   // current tile before it waits for a claimed item to be pushed, so holding
   // one claimed item per workgroup cannot stall the graph.
-  const int q = (int)(blockIdx.x % (unsigned)E.nq);
+  const int q = (int)(blockIdx.x % (unsigned)E.nq), lane = threadIdx.x % WAVE;
   int32_t *next = &E.ctrl[(q + 1) * (ENGINE_CTRL_LINE / 4)], *reserved = &E.ctrl[0], *err = &E.ctrl[1];
-  int w = 0;
-  if (threadIdx.x == 0) w = q + E.nq * add_i(next, 1);
-  for (;;) {
+  int claim = 0;  // the queue's counter as claimed: item q + claim x nq
+  unsigned long long item = 0;
+  if (threadIdx.x == 0) claim = add_i_later(next, 1);
+  for (int par = 0;; par ^= 1) {
     if (threadIdx.x == 0) {
       int task = -1, tile = 0;
+      const int w = q + E.nq * claim;
       if (w < E.total_tiles) {
         // wait until the push that reserves item w has filled it in
         long long spins = 0;
         int seen = -1;
-        for (;;) {
-          const unsigned long long v = ld_u64(&E.work[w]);
-          if (v != 0) {
-            task = (int)(unsigned)(v & 0xffffffffULL) - 1;
-            tile = (int)(v >> 32);
-            if (tile == 0 && E.tstart) E.tstart[task] = tick(E.clock);
-            break;
-          }
+        while (item == 0) {
           if (ld_i(err)) break;
           const int r = ld_i(reserved);
           if (r != seen) {
             seen = r;
             spins = 0;
           }
-          __builtin_amdgcn_s_sleep(2);
+          __builtin_amdgcn_s_sleep(1);
           if (++spins > E.spin_limit) {
             st_i(err, 1);
             break;
           }
+          item = ld_u64(&E.work[w]);
         }
-        if (task >= 0) w = q + E.nq * add_i(next, 1);
+        if (item != 0) {
+          task = (int)(unsigned)(item & 0xffffffffULL) - 1;
+          tile = (int)(item >> 32);
+          if (tile == 0 && E.tstart) E.tstart[task] = tick(E.clock);
+        }
       }
-      s_task = task;
-      s_tile = tile;
+      s_task[par] = task;
+      s_tile[par] = tile;
     }
     __syncthreads();
-    const int t = s_task, k = s_tile;
+    const int t = __builtin_amdgcn_readfirstlane(s_task[par]), k = __builtin_amdgcn_readfirstlane(s_tile[par]);
     if (t < 0) break;
-    const TaskD &d = E.tasks[t];
+    if (threadIdx.x == 0) claim = add_i_later(next, 1);
+    const TaskD d = load_task(E.tasks, t);
     float acc = d.red_op ? red_identity<float>(d.red_op) : 0.0f;
     run_tile(d, k, acc);
+    item = 0;
+    if (threadIdx.x == 0 && q + E.nq * claim < E.total_tiles) item = ld_u64(&E.work[q + E.nq * claim]);  // there already?
+    double partial = 0.0;
     if (d.red_op) {
-      const float wg = block_reduce(d.red_op, acc, s_red);
-      if (threadIdx.x == 0)
-        coh_store((unsigned long long *)&E.partials[d.part_base + k], __builtin_bit_cast(unsigned long long, (double)wg));
+      partial = (double)block_reduce(d.red_op, acc, s_red);  // in thread 0
+      if (d.ntiles > 1 && threadIdx.x == 0) {
+        coh_store((unsigned long long *)&E.partials[d.part_base + k], __builtin_bit_cast(unsigned long long, partial));
+        complete_own_accesses();
+      }
     }
     // Before the tile counts as done: a task whose data another task touches
     // has every thread's tile stores at the coherent level; otherwise only
     // the reduction partial (thread 0's store) must have landed: no other
     // task reads the data, and the kernel's end publishes it.
-    if (d.mem == MEM_COHERENT || (d.red_op && threadIdx.x == 0)) complete_own_accesses();
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = (add_i(&E.tiles_done[t], 1) == d.ntiles - 1);
-    __syncthreads();
-    if (s_last) {
-      if (d.red_op) {
-        double v = red_identity<double>(d.red_op);
-        for (int i = threadIdx.x; i < d.ntiles; i += blockDim.x)
-          v = red_apply(d.red_op, v,
-                        __builtin_bit_cast(double, coh_load((unsigned long long *)&E.partials[d.part_base + i])));
-        v = block_reduce(d.red_op, v, s_red64);
-        if (threadIdx.x == 0)
-          coh_store((unsigned long long *)d.result, __builtin_bit_cast(unsigned long long, red_apply(d.red_op, d.init, v)));
-      }
-      if (threadIdx.x == 0) {
-        if (E.tok) {
-          uint64_t hsh = mix64((uint64_t)(t + 1) * 0x9E3779B97F4A7C15ULL);
-          for (int i = d.pred_begin; i < d.pred_end; ++i)
-            hsh = mix64(hsh ^ coh_load((unsigned long long *)&E.tok[E.pred[i]]));
-          coh_store((unsigned long long *)&E.tok[t], hsh);
-        }
-        if (E.tdone) E.tdone[t] = tick(E.clock);
-        complete_own_accesses();  // result, token and stamp before any successor starts
-        for (int i = d.succ_begin; i < d.succ_end; ++i) {
-          const int s = E.succ[i];
-          if (add_i(&E.indeg[s], -1) == 1) {
-            const int nt = E.tasks[s].ntiles;
-            const int base = add_i(reserved, nt);
-            for (int q = 0; q < nt; ++q) st_u64(&E.work[base + q], work_item(s, q));
-          }
-        }
-      }
+    if (d.mem == MEM_COHERENT) {
+      complete_own_accesses();
+      __syncthreads();
     }
-    __syncthreads();
+    if (threadIdx.x < WAVE) {
+      int last = 1;
+      if (d.ntiles > 1) {
+        if (lane == 0) last = add_i(&E.tiles_done[t], 1) == d.ntiles - 1;
+        last = __builtin_amdgcn_readfirstlane(last);
+      }
+      if (last) finish_task(E, d, t, lane, partial);
+    }
   }
 }
 
@@ -576,7 +646,9 @@ static upir_status engine_prepare(upir_ctx *c, const upir_engine_sched &es, Engi
       d.a = p.a;
       d.x = p.x;
       d.y = p.y;
-      d.vec = d.step == 1 && ((uintptr_t)(p.x + d.lb) % 16 == 0) && ((uintptr_t)(p.y + d.lb) % 16 == 0);
+      // 16-byte accesses start at any element; a reduction keeps the order
+      // that its elements have always been folded in
+      d.vec = d.step == 1 && (d.red_op == RED_NONE || (((uintptr_t)(p.x + d.lb) % 16 == 0) && ((uintptr_t)(p.y + d.lb) % 16 == 0)));
     } else if (lp->kind == UPIR_BODY_SUM) {
       const SumP &p = *(const SumP *)pay;
       if (p.dtype != UPIR_DT_F32) return upir_fail(c, UPIR_EUNSUPPORTED, "batched SUM tasks take float32 data");
@@ -636,8 +708,17 @@ static upir_status engine_prepare(upir_ctx *c, const upir_engine_sched &es, Engi
   E.tstart = c->trace.start_stamp;
   E.tdone = c->trace.done_stamp;
   E.spin_limit = 1LL << 22;
+  // Workgroups per CU: streaming tiles keep 8 16-byte loads per lane in
+  // flight and reach their rate with two (2048 tasks of 2^8 .. 2^22 elements
+  // of the three bodies without edges: 931 us, with four 1005 us: more
+  // streams at once cost DRAM pages); a MATVEC tile waits on each row's
+  // reduction and wants four (MATVEC tasks alone 590 us, with two 709 us).
+  int64_t row_tiles = 0;
+  for (const TaskD &d : td)
+    if (d.kind == UPIR_BODY_MATVEC) row_tiles += d.ntiles;
+  int grid = c->num_cus * (2 * row_tiles > total_tiles ? 4 : 2);
+  grid = (int)std::min<int64_t>(grid, std::max<int64_t>(total_tiles, 1));  // one per item at most
   const char *gs = getenv("UPIR_ENGINE_GRID");
-  int grid = c->num_cus * 4;
   if (gs && atoi(gs) > 0) grid = atoi(gs);
   E.nq = std::min(grid, ENGINE_QUEUES);
   const int rgrid = (int)std::max<int64_t>(1, std::min<int64_t>(1024, (std::max<int64_t>(n, total_tiles) + 255) / 256));
