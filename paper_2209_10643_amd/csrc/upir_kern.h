@@ -41,7 +41,7 @@ struct SchedK {
   int32_t tile[3];
   int64_t t0[3], nt[3], ntiles;  // tile grid (tiled only)
   int32_t T, U;                   // teams, units of the launch
-  long long *dyn_next;            // DYNAMIC / GUIDED claim counter (self-resetting)
+  long long *dyn_next;            // DYNAMIC / GUIDED claim counters (self-resetting), SLOT_WORDS apart
   unsigned *dyn_exit;             // workgroups that finished claiming
 };
 
@@ -75,6 +75,7 @@ struct RedK {
 // stores to one line from many workgroups are serialised.
 constexpr unsigned long long SLOT_EMPTY = ~0ULL;
 constexpr int SLOT_WORDS = 16;  // 64-bit words between slots
+constexpr int DYN_QUEUES = 8;   // claim counters of a dynamic or guided schedule, one line each
 
 // ------------------------------------------------------------------ helpers
 // a / b for a >= 0, b > 0. A 64-bit division is some 150 instructions in a

@@ -93,3 +93,23 @@ def test_sum(ctx, dtype, pol, chunk, n, off, T, Uu):
             assert abs(got - want) <= bound
         else:
             assert got == (max if op == "max" else min)([1] + [e.item() for e in part])
+
+
+@pytest.mark.parametrize("T", [1, 63, 64, 95, 96, 255, 256, 257])
+@pytest.mark.parametrize("pol", [U.UPIR_SCHED_DYNAMIC, U.UPIR_SCHED_GUIDED])
+def test_claim_queues(ctx, pol, T):
+    # one to eight claim counters, ranges fewer and more than teams; each
+    # launch starts from the counters that the one before re-armed
+    for n in (0, 64, 64 * T - 1, 64 * T + 1, 64 * 7 * T + 33):
+        x, y = synth.uniform_pm1(52, 0, n + 1), synth.uniform_pm1(52, 1, n + 1)
+        tx, ty = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+        lp = ctx.loop(U.UPIR_BODY_AXPY, U.upir_axpy_args(2.5, 0, tx.data_ptr(), ty.data_ptr()), [(0, n, 1)],
+                      H.make_sched(pol, 1))
+        sp = H.make_spmd(T, 64)
+        want = y.copy()
+        for _ in range(4):
+            ctx.launch(lp, sp)
+            want[:n] = bodies.axpy(2.5, x[:n], want[:n])
+        ctx.sync()
+        ctx.free(lp)
+        assert np.array_equal(ty.cpu().numpy(), want), (n, T)
