@@ -921,6 +921,16 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
       if (is_matmul(lp->kind) || lp->kind == UPIR_BODY_JACOBI5 || lp->kind == UPIR_BODY_FILTER7) T = std::max<int64_t>(T, 1);
     } else if (lp->kind == UPIR_BODY_MATVEC && sp.num_units != dsp.num_units) {
       T = std::max<int64_t>(1, std::min<int64_t>(cdiv(L.n, 4), 8LL * c->num_cus));  // teams of a size the default is not for
+    } else if (lp->kind == UPIR_BODY_AXPY && S.policy == POL_STATIC && S.dist == UPIR_DIST_TEAMS_UNITS &&
+               L.step[0] == 1 && !lp->has_red && L.n >= (8LL << 20)) {
+      // Static blocks of a few resident teams are as many separate streams,
+      // which cost HBM pages: 102,400,000 elements took 232 us with the
+      // default teams, 187 us with blocks of 16 elements a unit (one pass of
+      // the loads that a lane keeps in flight), started in memory order as
+      // teams leave; 8 elements a unit 205 us, 32 198 us. 20,000,001: 50
+      // against 39 us; 10,000,000: 23.0 against 22.3; 5,000,000, which the
+      // caches hold: 9.5 against 10.2. A reduction would fold a partial a team.
+      T = cdiv(L.n, 16LL * std::max(sp.num_units, 256));
     } else {
       T = dsp.num_teams > 0 ? dsp.num_teams : 1;
     }

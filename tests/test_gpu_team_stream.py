@@ -113,3 +113,16 @@ def test_claim_queues(ctx, pol, T):
         ctx.sync()
         ctx.free(lp)
         assert np.array_equal(ty.cpu().numpy(), want), (n, T)
+
+
+@pytest.mark.parametrize("n", [(8 << 20) - 1, (8 << 20) + 1])
+def test_static_default_teams(ctx, n):
+    # either side of the size from which static blocks are one pass long
+    x, y = synth.uniform_pm1(53, 0, n), synth.uniform_pm1(53, 1, n)
+    tx, ty = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    lp = ctx.loop(U.UPIR_BODY_AXPY, U.upir_axpy_args(2.5, 0, tx.data_ptr(), ty.data_ptr()), [(0, n, 1)],
+                  H.make_sched(U.UPIR_SCHED_STATIC))
+    ctx.launch(lp)
+    ctx.sync()
+    ctx.free(lp)
+    assert np.array_equal(ty.cpu().numpy(), bodies.axpy(2.5, x, y))
