@@ -1067,7 +1067,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": JACOBI_4096_TRAFFIC.get((jw.tile[0], jw.units)),
                 "traffic_source": "rocprofv3 FETCH_SIZE / WRITE_SIZE per launch shape, profiles/jacobi5_4096_hbm_traffic.md",
-                "kernel": f"k_jacobi_tile<{jw.tile[0]},RED_MAX> ({jw.units} units, deferred fold)", "avg_launch_us": round(sweep_ms * 1e3, 3),
+                "kernel": f"k_jacobi_tile<RED_MAX> ({jw.tile[0]}-row tiles, {jw.units} units, deferred fold)", "avg_launch_us": round(sweep_ms * 1e3, 3),
                 "algorithmic_bytes_per_launch": jw.bytes_per_sweep(),
                 "residency": "the two 64 MiB grids stay in the 256 MB MALL between sweeps, so this is a "
                              "cache-resident rate priced against the HBM peak; the HBM-bound form of the same "

@@ -257,7 +257,7 @@ upir_status upir_reduce(upir_ctx *ctx, int32_t op, int32_t dtype, const void *de
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * reduction of upir_reduce, with the same arguments, kernels and results,
  * that allocates nothing. Its reduction scratch is a static device array of
- * 256 + 128 x UPIR_REDUCE_NOALLOC_MAX_TEAMS bytes that every GPU the library
+ * 1280 + 128 x UPIR_REDUCE_NOALLOC_MAX_TEAMS bytes that every GPU the library
  * runs on holds until the process ends. Differences from upir_reduce:
  *  - red->result must be a device address (result_on_host = 0; else
  *    UPIR_EINVAL); the call only enqueues, and the result is defined in

@@ -786,6 +786,10 @@ __global__ void __launch_bounds__(1024) k_matvec(LoopK L, SchedK S, MatvecP p, R
     const int64_t stride = (int64_t)S.T * NW;
     int64_t k = (int64_t)blockIdx.x * NW + w;
     for (; k + (RW - 1) * stride < L.n; k += RW * stride) rows(std::integral_constant<int, RW>{}, k, stride);
+    if (RW > 2 && k + stride < L.n) {
+      rows(std::integral_constant<int, 2>{}, k, stride);
+      k += 2 * stride;
+    }
     for (; k < L.n; k += stride) rows(std::integral_constant<int, 1>{}, k, stride);
   } else {
     SchedK SW = S;
@@ -808,11 +812,11 @@ hipError_t launch_matvec_wave(const MatvecP &p, const LoopK &L, const SchedK &S,
   const int64_t waves = (int64_t)S.T * (S.U / WAVE);
   const bool strided = S.policy == POL_CHUNK && S.chunk == 1 && S.dist == DIST_TU;
   if (R.op != RED_NONE) {
-    if (strided && L.n >= 4 * waves) go_matvec<4, true>(nt, p, L, S, R, st);
+    if (strided && L.n > 3 * waves) go_matvec<4, true>(nt, p, L, S, R, st);
     else go_matvec<1, true>(nt, p, L, S, R, st);
   } else {
-    if (strided && L.n >= 4 * waves) go_matvec<4, false>(nt, p, L, S, R, st);
-    else if (strided && L.n >= 2 * waves) go_matvec<2, false>(nt, p, L, S, R, st);
+    if (strided && L.n > 3 * waves) go_matvec<4, false>(nt, p, L, S, R, st);
+    else if (strided && L.n > waves) go_matvec<2, false>(nt, p, L, S, R, st);
     else go_matvec<1, false>(nt, p, L, S, R, st);
   }
   return hipGetLastError();

@@ -797,12 +797,32 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         // 13.3 us, 19.2 four to a team; 300 x 5000: 4.9 and 5.9)
         sp.num_teams = (int32_t)std::max<int64_t>(1, n);
         sp.num_units = 64;
-      } else if (n * cols >= (128LL << 20) && n >= 8 * cus && !lp->has_red) {
-        // 512 MiB of A and more: eight wavefronts per CU (16384 x 16384: 154
-        // us with 2,048 of them, 181 with 8,192; 4096 x 40000: 100 and 103;
-        // at 5376 x 20972, 430 MiB, 81 and 78)
-        sp.num_teams = (int32_t)cus;
-        sp.num_units = 512;
+      } else if (n >= 8 * cus && !lp->has_red &&
+                 n * cols >= (n < 32 * cus ? 48LL << 20 : 128LL << 20)) {
+        // Large matrices are bound by how evenly the rows come out over the
+        // CUs. Eight wavefronts per CU where they do (8192 x 24414: 125 us,
+        // with 8,192 wavefronts 130). Otherwise teams of one wavefront, as
+        // many as leave the CUs the most even number of rows at one, two or
+        // four rows a wavefront; rows that share x are worth 4% of that
+        // (4694 x 42607: 134 us, with eight wavefronts per CU 158; 2500 x
+        // 80000: 120, with four-wavefront teams of a row each 143; 2500 x
+        // 24000: 38 and 44). From 8,192 rows on the 192 MiB matrices have
+        // enough of them either way (14000 x 4285: 40 and 38).
+        const int64_t per = cdiv(n, 8 * cus);  // rows a wavefront, eight per CU
+        if (n * cols >= (128LL << 20) && per % 2 == 0 && n * 100 >= per * 8 * cus * 98) {
+          sp.num_teams = (int32_t)cus;
+          sp.num_units = 512;
+        } else {
+          double best = 0.0;
+          for (int r = 1; r <= 4; r *= 2) {
+            const int64_t waves = cdiv(n, r);
+            const double even = (r > 1 ? 1.04 : 1.0) * (double)n / (double)(cdiv(waves, cus) * cus * r);
+            if (even < best || (r == 4 && 10 * waves < 39 * cus)) continue;
+            best = even;
+            sp.num_teams = (int32_t)std::min<int64_t>(waves, 1 << 20);
+            sp.num_units = 64;
+          }
+        }
       } else {
         sp.num_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
       }

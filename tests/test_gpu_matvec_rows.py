@@ -79,3 +79,29 @@ def test_strided_rows_and_reduction(ctx):
         rest = np.setdiff1d(np.arange(rows), idx)
         assert (got[rest] == -7.0).all()
         assert r.item() == float(got[idx].max())
+
+
+@pytest.mark.parametrize("rows", [8, 9, 15, 16, 17, 24, 25, 28, 31, 32, 33, 40, 41, 47, 48, 63, 65])
+def test_rows_left_over(ctx, rows):
+    # eight wavefronts: some with four, three, two, one or no rows of a round
+    cols = 1030
+    A = synth.uniform_pm1(73, 0, rows * cols).reshape(rows, cols)
+    x = synth.uniform_pm1(73, 1, cols)
+    chunk1, one = H.make_sched(U.UPIR_SCHED_STATIC_CHUNK, 1), H.make_sched(U.UPIR_SCHED_STATIC_CHUNK, 2)
+    got = run(ctx, A, x, 2, 1, [(0, rows, 1)], chunk1, H.make_spmd(8, 64))
+    assert bodies.frob_rel(got, bodies.matvec(A, x)) <= 1e-5
+    assert np.array_equal(got, run(ctx, A, x, 2, 1, [(0, rows, 1)], one, H.make_spmd(8, 64)))
+
+
+@pytest.mark.parametrize("rows,cols", [(2100, 24000), (4096, 32770), (4694, 28600)])
+def test_default_teams_of_large_matrices(ctx, rows, cols):
+    # few rows, rows that come out even over the CUs, rows that do not
+    A = torch.randn(rows, cols, device="cuda")
+    x, y, z = torch.randn(cols, device="cuda"), torch.zeros(rows, device="cuda"), torch.zeros(rows, device="cuda")
+    for out, sched, spmd in ((y, None, None), (z, H.make_sched(U.UPIR_SCHED_STATIC_CHUNK, 2), H.make_spmd(64, 256))):
+        lp = ctx.loop(U.UPIR_BODY_MATVEC, U.upir_matvec_args(A.data_ptr(), x.data_ptr(), out.data_ptr(), cols, cols),
+                      [(0, rows, 1)], sched)
+        ctx.launch(lp, spmd)
+        ctx.sync()
+        ctx.free(lp)
+    assert torch.equal(y, z)
