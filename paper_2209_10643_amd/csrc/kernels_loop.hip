@@ -423,15 +423,18 @@ constexpr int JT_W = 256;  // tile width (points)
 // Residual reduction. The float64 value of |u1 - u0| is only needed where it
 // can change the maximum (or minimum): rounding to float32 is monotonic, so a
 // point whose float32 |u1 - u0| is below a maximum already found cannot hold
-// the exact one. The threshold is the wavefront's, over all its lanes: a row
-// of 256 points passes the r - 1 rows before it with chance 1 / r, so a strip
-// of sixteen rows takes the float64 path about three times. (With a threshold
-// per lane some lane of the 64 passed its own in nearly every row.) Only
-// candidates at or above it take that path; the result is exact.
+// the exact one. Each lane has a threshold of its own, its best so far, and in
+// a strip of at most four rows (the default shape of a deferred residual) also
+// the wavefront's best of the first row: 23.4 us a sweep of 4096 x 4096, with
+// the lanes' own alone 24.2. In longer strips the lanes' own do as well, and
+// on a smooth grid, whose updates grow along a strip, sharing the wavefront's
+// after every hit cost 1 to 3%. Only candidates at or above the threshold take
+// the float64 path; the result is exact.
 template <int OP>
 struct ResidualAcc {
   float m32 = OP == RED_MIN ? __builtin_inff() : -1.0f;  // this lane's best candidate, in float32
-  float w32 = m32;                                       // the wavefront's
+  float w32 = m32;                                       // below (above) it no point of this lane can matter
+  bool share = false;                                    // the wavefront's best is still to be shared
   double m64 = OP == RED_SUM ? 0.0 : (OP == RED_MAX ? -__builtin_inf() : __builtin_inf());
   __device__ void add(float v, float c) {
     if (OP == RED_SUM) {
@@ -454,22 +457,30 @@ struct ResidualAcc {
     const float o = dpp_move<CTRL, RM>(v, v);
     return OP == RED_MAX ? fmaxf(v, o) : fminf(v, o);
   }
-  // The four points of a lane's row; bit e of `mk` marks point e as in the
-  // loop box. Every lane of the wavefront calls it.
-  __device__ void add4(const f32x4 &v, const f32x4 &c, int mk) {
-    if (OP != RED_SUM) {
-      constexpr float NONE = OP == RED_MAX ? -1.0f : __builtin_inff();
-      const float d0 = mk & 1 ? fabsf(v.x - c.x) : NONE, d1 = mk & 2 ? fabsf(v.y - c.y) : NONE;
-      const float d2 = mk & 4 ? fabsf(v.z - c.z) : NONE, d3 = mk & 8 ? fabsf(v.w - c.w) : NONE;
-      const float dm = OP == RED_MAX ? fmaxf(fmaxf(d0, d1), fmaxf(d2, d3)) : fminf(fminf(d0, d1), fminf(d2, d3));
-      if (__builtin_amdgcn_ballot_w64(OP == RED_MAX ? dm >= w32 : dm <= w32) == 0) return;
-    }
+  __device__ void points(const f32x4 &v, const f32x4 &c, int mk) {
     if (mk & 1) add(v.x, c.x);
     if (mk & 2) add(v.y, c.y);
     if (mk & 4) add(v.z, c.z);
     if (mk & 8) add(v.w, c.w);
-    if (OP != RED_SUM) {  // the wavefront's best, by the steps of its reduction tree
-      float w = m32;
+  }
+  // The four points of a lane's row; bit e of `mk` marks point e as in the
+  // loop box. Every lane of the wavefront calls it.
+  __device__ void add4(const f32x4 &v, const f32x4 &c, int mk) {
+    if (OP == RED_SUM) {
+      points(v, c, mk);
+      return;
+    }
+    constexpr float NONE = OP == RED_MAX ? -1.0f : __builtin_inff();
+    const float d0 = mk & 1 ? fabsf(v.x - c.x) : NONE, d1 = mk & 2 ? fabsf(v.y - c.y) : NONE;
+    const float d2 = mk & 4 ? fabsf(v.z - c.z) : NONE, d3 = mk & 8 ? fabsf(v.w - c.w) : NONE;
+    const float dm = OP == RED_MAX ? fmaxf(fmaxf(d0, d1), fmaxf(d2, d3)) : fminf(fminf(d0, d1), fminf(d2, d3));
+    if (OP == RED_MAX ? dm >= w32 : dm <= w32) {
+      points(v, c, mk);
+      w32 = OP == RED_MAX ? fmaxf(w32, m32) : fminf(w32, m32);
+    }
+    if (share) {  // by the steps of the reduction tree
+      share = false;
+      float w = w32;
       w = best<0xB1, 0xF>(w);
       w = best<0x4E, 0xF>(w);
       w = best<0x141, 0xF>(w);
@@ -606,11 +617,16 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), NW = blockDim.x / WAVE;
   // The launch's cross-workgroup work goes to one extra workgroup that is
   // given no tile. The combine of this loop's own synchronous reduction waits
-  // for every other workgroup and must be launched last; the fold of an
-  // earlier loop's deferred reduction waits for none and is launched first,
-  // so that it runs beside the tiles however many rounds of them there are.
-  const bool xwg = jacobi_extra_wg(R), combine = RED && !R.defer, first = xwg && !combine;
-  const int G = xwg ? gridDim.x - 1 : gridDim.x, wg = (int)blockIdx.x - (first ? 1 : 0);
+  // for every other workgroup and must be launched last. The fold of an
+  // earlier loop's deferred reduction waits for none: with more than 16
+  // wavefronts of tiles per CU it is launched first, so that it runs beside
+  // the tiles and not after the last round of them (4096 x 4096, 16-row
+  // tiles on 256 units: 23.4 us, launched last 29.4); where all of the tiles
+  // start at once, last (128-row tiles on 512 units: 24.3 us, first 24.8).
+  const bool xwg = jacobi_extra_wg(R), combine = RED && !R.defer;
+  const int G = xwg ? gridDim.x - 1 : gridDim.x;
+  const bool first = xwg && !combine && (int64_t)G * NW > 16 * 256;
+  const int wg = (int)blockIdx.x - (first ? 1 : 0);
   if (xwg && wg == (first ? -1 : G)) {
     if (R.fold.count > 0) run_fold(R.fold);
     if (combine) finish_reduction<double>(R, ResidualAcc<RED>().m64);
@@ -622,6 +638,7 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   const int64_t jlo = L.lb[1], jhi = L.lb[1] + L.cnt[1];
   const int ld = (int)p.ld;
   ResidualAcc<RED> acc;
+  acc.share = SH <= 4;
 
   auto do_tile = [&](int64_t m) {
     const int64_t mi = quot(m, S.nt[1]), ti = S.t0[0] + mi, tj = S.t0[1] + (m - mi * S.nt[1]);
