@@ -196,11 +196,12 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
   int64_t lo, hi;
   while (ranges.next(lo, hi)) {
     // elements up to the first 16-byte boundary of the array that is written
-    // (or read, for SUM), one per lane; x may stay unaligned beside y
+    // (or read, for SUM), side by side (at most three, which a team of one or
+    // two units takes in turn); x may stay unaligned beside y
     const uintptr_t at = (uintptr_t)(AXPY ? (const T *)y + lo : x + lo);
     int64_t head = ((0 - at) & 15) / sizeof(T);
     if (head > hi - lo) head = hi - lo;
-    if (tid < head) one(lo + tid);
+    for (int64_t i = tid; i < head; i += U) one(lo + i);
     lo += head;
     const int64_t nv = (hi - lo) / W;
     const V *xv = (const V *)(x + lo);
@@ -229,8 +230,7 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
       for (int u = 0; u < UN - 1; ++u)
         if (m + (int64_t)u * U < nv) vec(xb[u], yb[u], yv + m + u * U);
     }
-    const int64_t tail = lo + nv * W + tid;
-    if (tail < hi) one(tail);
+    for (int64_t i = lo + nv * W + tid; i < hi; i += U) one(i);  // at most three, as at the start
   }
   if constexpr (OP != RED_NONE) finish_reduction<A>(R, acc);
   fold_hook(R);
