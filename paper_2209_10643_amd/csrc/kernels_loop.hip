@@ -238,9 +238,12 @@ hipError_t launch_generic(int32_t body, const void *payload, const LoopK &L, con
 
 // ------------------------------------------------- 1-D streaming, chunk 4
 // Ownership: chunk m (4 iterations) belongs to flat unit m mod (T U), flat =
-// team U + unit, exactly the static-chunk-4 schedule. x and y point at the
-// element of the first iteration; a chunk is one 16-byte access whatever its
-// alignment (the device takes element-aligned ones; a loop that starts
+// team U + unit: the static-chunk-4 schedule, exactly so where a float32 sum's
+// order or COVER's counters could show it. Otherwise the chunks are counted
+// from the first 16-byte boundary on, up to three iterations later, and the
+// `head` iterations before it go to the first units. x and y point at the
+// element of the first whole chunk; a chunk is one 16-byte access whatever
+// its alignment (the device takes element-aligned ones; a loop that starts
 // inside an array used to fall back to the schedule-exact kernel: 42 us
 // for 5,000,003 elements from element 1). Four owned chunks
 // of each input (eight for SUM) are loaded before any is used to keep
@@ -286,9 +289,9 @@ __global__ void __launch_bounds__(1024) k_stream4(int64_t n, float a, const floa
   };
   int64_t m = f;
   if (BODY == 1) {  // AXPY
-    if (f < head) {  // elements before the first whole chunk
-      const float r = __builtin_fmaf(a, x[f - head], y[f - head]);
-      y[f - head] = r;
+    for (int64_t i = f; i < head; i += F) {  // elements before the first whole chunk (a launch may have one unit)
+      const float r = __builtin_fmaf(a, x[i - head], y[i - head]);
+      y[i - head] = r;
       fold(r);
     }
     for (; m + 3 * F < nc; m += 4 * F) {
@@ -327,7 +330,7 @@ __global__ void __launch_bounds__(1024) k_stream4(int64_t n, float a, const floa
       }
     }
   } else if (BODY == 2) {  // SUM over float32: eight chunks in flight (one input stream)
-    if (f < head) fold(x[f - head]);
+    for (int64_t i = f; i < head; i += F) fold(x[i - head]);
     for (; m + 7 * F < nc; m += 8 * F) {
       f32x4 xv[8];
 #pragma unroll

@@ -105,3 +105,10 @@ def test_axpy(ctx, pol, chunk, T, Uu):
 @pytest.mark.parametrize("T,Uu", SPMD)
 def test_sum(ctx, dtype, pol, chunk, T, Uu):
     check_sum(ctx, dtype, pol, chunk, T, Uu)
+
+
+# chunk 4 over the flat unit number: the launch as a whole has one to three units
+@pytest.mark.parametrize("T,Uu", [(1, 1), (1, 2), (2, 1), (1, 3), (3, 1)])
+def test_chunk4(ctx, T, Uu):
+    check_axpy(ctx, U.UPIR_SCHED_STATIC_CHUNK, 4, T, Uu)
+    check_sum(ctx, "f32", U.UPIR_SCHED_STATIC_CHUNK, 4, T, Uu)
