@@ -667,8 +667,11 @@ upir_status resolve_payload(upir_ctx *c, upir_loop_obj *lp, unsigned char *paylo
 static int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Library default schedule and geometry for a body (used by AUTO when the
-// tuner and the model have nothing to say, and to fill num_teams = 0).
-void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc) {
+// tuner and the model have nothing to say, and to fill num_teams = 0 and
+// num_units = 0). `given` is the caller's launch shape, `fixed` the caller's
+// schedule (null: both free): what they set, the rest is chosen to fit.
+void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc, const upir_spmd *given,
+                    const upir_sched *fixed) {
   const int64_t n = lp->n;
   const int64_t cap = 8LL * c->num_cus;
   sc = upir_sched{};
@@ -746,7 +749,10 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // x (nanoseconds of a tile per k, measured with every CU busy), plus
       // the pre-pass of the tiles that read bfloat16 operands from the
       // workspace: 5 us and its bytes at 5.5 TB/s. `per` tiles of a kind run
-      // on a CU together. What it decides between, measured (us):
+      // on a CU together, and of all kinds no more than the caller's teams
+      // (float32 512^3 on 16 teams: 128 x 128, 41 us; bfloat16 1024^3 on 16:
+      // 256 x 256, 28 us, 73 on 128 x 128). What it decides between, measured
+      // (us):
       //   float32   512^3    7 (32 x 32)     14 (64 x 64)    41 (128 x 128)
       //            1024^3   25 (64 x 64)     31 (32 x 32)    76 (128 x 128)
       //            2000^3  152 (128 x 128)  170 (64 x 64)   262 (256 x 128)
@@ -771,14 +777,28 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       const bool is_f32 = lp->kind == UPIR_BODY_MATMUL_F32, is_split = lp->kind == UPIR_BODY_MATMUL_SPLIT3;
       const Tile *tiles = is_f32 ? f32 : is_split ? split : bf16;
       const int64_t M = lp->cnt[0], N = lp->cnt[1], K = ((const upir_matmul_args *)lp->args)->K;
+      // A tile runs on the units that its kernel is built for and on no other
+      // number (the one-point-per-unit kernel is left then, 9.9 ms instead of
+      // 20 us for the split product of 1000 x 777 by 777 x 1300), so units
+      // that the caller gives bound the tiles, and a tile that the caller
+      // names, the units; without one that fits, neither does.
+      const int32_t units = given ? given->num_units : 0;
+      const bool named = fixed && fixed->policy != UPIR_SCHED_AUTO && fixed->tile[0] > 0;
+      bool fits = false;
+      for (int i = 0; i < (is_f32 ? 5 : 6); ++i)
+        fits = fits || ((!units || tiles[i].units == units) &&
+                        (!named || (tiles[i].bm == fixed->tile[0] && tiles[i].bn == fixed->tile[1])));
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = 0;
       double best = 0.0;
       for (int i = 0; i < (is_f32 ? 5 : 6); ++i) {
         const Tile &t = tiles[i];
+        if (fits && ((units && t.units != units) || (named && (t.bm != fixed->tile[0] || t.bn != fixed->tile[1])))) continue;
         // the 256 x 256 tile addresses each operand with 32-bit offsets
         if (t.pre && t.bm == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;
-        double us = 1e-3 * t.ns * (double)K * (double)cdiv(cdiv(M, t.bm) * cdiv(N, t.bn), (int64_t)t.per * c->num_cus);
+        int64_t at_once = (int64_t)t.per * c->num_cus;
+        if (given && given->num_teams > 0) at_once = std::min<int64_t>(at_once, given->num_teams);
+        double us = 1e-3 * t.ns * (double)K * (double)cdiv(cdiv(M, t.bm) * cdiv(N, t.bn), at_once);
         if (t.pre) us += 5.0 + (double)(M + N) * (double)K * (is_split ? 8.0 : 6.0) / 5.5e6;
         if (sc.tile[0] == 0 || us < best) {
           best = us;
@@ -863,7 +883,7 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
   upir_sched sc = lp->sched;
   upir_spmd dsp;
   upir_sched dsc;
-  default_choice(c, lp, dsp, dsc);
+  default_choice(c, lp, dsp, dsc, &sp, &sc);
   if (sc.policy == UPIR_SCHED_RUNTIME) {
     upir_sched r{};
     if (!parse_runtime_schedule(r)) return upir_fail(c, UPIR_EINVAL, "UPIR_SCHEDULE is malformed");
@@ -882,7 +902,8 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     } else if (c->model_on) {
       model_pick(c, lp, asp, asc);
     }
-    sc = asc;
+    // a tuned or predicted tile for other units than the caller's has no kernel
+    sc = is_matmul(lp->kind) && sp.num_units != 0 && sp.num_units != asp.num_units ? dsc : asc;
     if (sp.num_teams == 0) sp.num_teams = asp.num_teams;
     if (sp.num_units == 0) sp.num_units = asp.num_units;
   }

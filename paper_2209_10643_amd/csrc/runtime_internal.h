@@ -172,7 +172,8 @@ bool candidate_at(upir_ctx *c, const upir_loop_obj *lp, int idx, upir_spmd &sp, 
 void candidate_features(upir_ctx *c, const upir_loop_obj *lp, const upir_spmd &sp, const upir_sched &sc,
                         float f[32]);
 bool model_pick(upir_ctx *c, upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc);
-void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc);
+void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sched &sc,
+                    const upir_spmd *given = nullptr, const upir_sched *fixed = nullptr);
 // Engine schedules of the batched executor: candidates (0 = default), the
 // shape key of the pending task graph, features of (graph, candidate), and
 // the cost model's pick among the candidates (false when the model is off).

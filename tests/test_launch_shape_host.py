@@ -1,0 +1,96 @@
+"""Launch shapes that the caller gives in part (teams, units, or a tile): what
+the library fills in fits them. Resolved on a host-only context (CPU), and for
+choices that need a device, on the GPU.
+"""
+import ctypes as C
+
+import pytest
+
+from paper_2209_10643_amd import helpers as H
+from paper_2209_10643_amd import upir as U
+
+_buf = C.create_string_buffer(1 << 21)  # resolving reads no memory: every allocation may be this block
+_BASE = (C.addressof(_buf) + 255) // 256 * 256
+
+
+@U.ALLOC_FN
+def _alloc(n, user):
+    return _BASE
+
+
+@U.FREE_FN
+def _free(p, user):
+    pass
+
+
+@pytest.fixture(scope="module")
+def hctx():
+    h = C.c_void_p()
+    U.upir_init(U.UPIR_DEVICE_NONE, None, C.byref(h))
+    U.upir_set_allocator(h, _alloc, _free, None)
+    yield h
+    U.upir_finalize(h)
+
+
+def resolve(h, kind, args, dims, sched=None, spmd=(0, 0), red=None):
+    body = U.upir_body(kind, 1, C.cast(C.pointer(args), C.c_void_p), C.sizeof(args))
+    L, lp = H.make_loop(dims), C.c_void_p()
+    U.upir_loop_parallel(h, C.byref(L), C.byref(sched) if sched else None, C.byref(body),
+                         C.byref(red) if red else None, C.byref(lp))
+    sp, sc, v, want = U.upir_spmd(), U.upir_sched(), C.c_int32(), H.make_spmd(*spmd)
+    U.upir_loop_resolve(h, C.byref(want), lp, C.byref(sp), C.byref(sc), C.byref(v))
+    U.upir_loop_free(h, lp)
+    return U.VARIANTS[v.value], sp.num_teams, sp.num_units, (sc.tile[0], sc.tile[1])
+
+
+KINDS = {"f32": U.UPIR_BODY_MATMUL_F32, "bf16": U.UPIR_BODY_MATMUL_BF16, "split": U.UPIR_BODY_MATMUL_SPLIT3}
+MMN = [(16, 16, 16), (64, 64, 64), (512, 512, 512), (1000, 1300, 776), (1024, 1024, 1024), (2000, 2000, 2000),
+       (4096, 4096, 4096)]
+
+
+def matmul(h, kind, M, N, K, sched=None, spmd=(0, 0)):
+    args = U.upir_matmul_args(0x10000000, 0x20000000, 0x30000000, K, K, N, N, None, 0)
+    return resolve(h, KINDS[kind], args, [(0, M, 1), (0, N, 1)], sched, spmd)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("M,N,K", MMN)
+def test_matmul_auto_fits_the_units(hctx, kind, M, N, K):
+    for teams in (0, 16):
+        for units in (0, 256, 512):
+            variant, T, Uu, tile = matmul(hctx, kind, M, N, K, None, (teams, units))
+            assert variant == "matmul_mfma", (teams, units, tile)
+            assert units in (0, Uu) and teams in (0, T)
+
+
+def test_matmul_tile_for_few_teams(hctx):
+    # 16 teams run the 16 tiles of 128 x 128 at once, 64 tiles of 64 x 64 in four rounds
+    assert matmul(hctx, "f32", 512, 512, 512, None, (16, 0))[3] == (128, 128)
+    assert matmul(hctx, "f32", 512, 512, 512)[3] == (32, 32)
+
+
+@pytest.mark.parametrize("kind,tile,units", [
+    ("f32", (256, 128), {512}), ("f32", (128, 128), {256}), ("f32", (64, 128), {512}), ("f32", (64, 64), {512}),
+    ("f32", (32, 32), {512})] + [(k, t, u) for k in ("bf16", "split") for t, u in (
+        ((256, 256), {256}), ((128, 128), {256, 512}), ((64, 128), {512}), ((64, 64), {512}), ((32, 32), {512}))])
+def test_matmul_units_fit_the_tile(hctx, kind, tile, units):
+    for M, N, K in MMN:
+        for pol, chunk in ((U.UPIR_SCHED_STATIC, 0), (U.UPIR_SCHED_STATIC_CHUNK, 2)):
+            for teams in (0, 16):
+                variant, _, Uu, t = matmul(hctx, kind, M, N, K, H.make_sched(pol, chunk, tile=tile), (teams, 0))
+                assert variant == "matmul_mfma" and Uu in units and t == tile, (M, N, K, teams)
+
+
+@pytest.mark.gpu
+def test_matmul_tuned_choice_fits_the_units():
+    torch = pytest.importorskip("torch")
+    n = 512
+    A, Cm = torch.rand(n, n, device="cuda"), torch.zeros(n, n, device="cuda")
+    with H.Context(0) as ctx:
+        args = U.upir_matmul_args(A.data_ptr(), A.data_ptr(), Cm.data_ptr(), n, n, n, n, None, 0)
+        lp = ctx.loop(U.UPIR_BODY_MATMUL_BF16, args, [(0, n, 1), (0, n, 1)])
+        U.upir_tune(ctx.h, None, lp, 3, None, None, None)
+        for units in (0, 256, 512):
+            sp, sc, v = ctx.resolve(lp, H.make_spmd(0, units))
+            assert U.VARIANTS[v] == "matmul_mfma" and units in (0, sp.num_units), (units, sp.num_units, sc.tile[0])
+        ctx.free(lp)
