@@ -813,15 +813,23 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       const int64_t cols = ((const upir_matvec_args *)lp->args)->cols, cus = c->num_cus;
       sc.policy = UPIR_SCHED_STATIC_CHUNK;
       sc.chunk = 1;
-      if (n < 4 * cus && !lp->has_red) {  // a wavefront per row on CUs of their own (255 x 39807:
-        // 13.3 us, 19.2 four to a team; 300 x 5000: 4.9 and 5.9)
+      const bool own = fixed && fixed->policy != UPIR_SCHED_AUTO;  // the caller's schedule
+      const bool chunk1 = !own || (fixed->policy == UPIR_SCHED_STATIC_CHUNK && fixed->chunk == 1 &&
+                                   fixed->distribute == UPIR_DIST_TEAMS_UNITS);
+      const int32_t rest_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
+      sp.num_teams = rest_teams;
+      if (!lp->has_red && n < 4 * cus) {
+        // a wavefront per row on CUs of their own (255 x 39807: 13.3 us, 19.2
+        // four to a team; 300 x 5000: 4.9 and 5.9)
         sp.num_teams = (int32_t)std::max<int64_t>(1, n);
         sp.num_units = 64;
-      } else if (n >= 8 * cus && !lp->has_red &&
-                 n * cols >= (n < 32 * cus ? 48LL << 20 : 128LL << 20)) {
+      } else if (!lp->has_red && n >= 8 * cus && n * cols >= (n < 32 * cus ? 48LL << 20 : 128LL << 20)) {
         // Large matrices are bound by how evenly the rows come out over the
         // CUs. Eight wavefronts per CU where they do (8192 x 24414: 125 us,
-        // with 8,192 wavefronts 130). Otherwise teams of one wavefront, as
+        // with 8,192 wavefronts 130), if the rows are dealt one by one: in
+        // blocks or chunks a wavefront takes its rows alone (8192 x 24414 in
+        // static blocks: 138 us, with 8,192 wavefronts 128; 16384 x 16384 in
+        // chunks of 16: 283 and 170). Otherwise teams of one wavefront, as
         // many as leave the CUs the most even number of rows at one, two or
         // four rows a wavefront; rows that share x are worth 4% of that
         // (4694 x 42607: 134 us, with eight wavefronts per CU 158; 2500 x
@@ -830,8 +838,10 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         // enough of them either way (14000 x 4285: 40 and 38).
         const int64_t per = cdiv(n, 8 * cus);  // rows a wavefront, eight per CU
         if (n * cols >= (128LL << 20) && per % 2 == 0 && n * 100 >= per * 8 * cus * 98) {
-          sp.num_teams = (int32_t)cus;
-          sp.num_units = 512;
+          if (chunk1) {
+            sp.num_teams = (int32_t)cus;
+            sp.num_units = 512;
+          }
         } else {
           double best = 0.0;
           for (int r = 1; r <= 4; r *= 2) {
@@ -843,8 +853,16 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
             sp.num_units = 64;
           }
         }
-      } else {
-        sp.num_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
+      }
+      // Teams and units above go together. Beside the caller's own number of
+      // the one, the other is 256 units, or a team per four rows: the caller's
+      // teams of one wavefront would have a quarter of the wavefronts (300 x
+      // 5000 on 16 teams: 16 instead of 64), and so would the one team of
+      // distribute(units).
+      if ((given && (given->num_teams > 0 || (given->num_units > 0 && given->num_units != sp.num_units))) ||
+          (own && fixed->distribute == UPIR_DIST_UNITS)) {
+        sp.num_teams = rest_teams;
+        sp.num_units = 256;
       }
       break;
     }
@@ -960,8 +978,6 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     if (S.tiled) {
       T = S.policy == UPIR_SCHED_STATIC ? S.ntiles : cdiv(S.ntiles, S.chunk);
       if (is_matmul(lp->kind) || lp->kind == UPIR_BODY_JACOBI5 || lp->kind == UPIR_BODY_FILTER7) T = std::max<int64_t>(T, 1);
-    } else if (lp->kind == UPIR_BODY_MATVEC && sp.num_units != dsp.num_units) {
-      T = std::max<int64_t>(1, std::min<int64_t>(cdiv(L.n, 4), 8LL * c->num_cus));  // teams of a size the default is not for
     } else if (lp->kind == UPIR_BODY_AXPY && S.policy == POL_STATIC && S.dist == UPIR_DIST_TEAMS_UNITS &&
                L.step[0] == 1 && !lp->has_red && L.n >= (8LL << 20)) {
       // Static blocks of a few resident teams are as many separate streams,

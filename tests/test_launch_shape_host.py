@@ -81,6 +81,28 @@ def test_matmul_units_fit_the_tile(hctx, kind, tile, units):
                 assert variant == "matmul_mfma" and Uu in units and t == tile, (M, N, K, teams)
 
 
+@pytest.mark.parametrize("pol,chunk", [(U.UPIR_SCHED_AUTO, 0), (U.UPIR_SCHED_STATIC, 0), (U.UPIR_SCHED_STATIC_CHUNK, 1),
+                                       (U.UPIR_SCHED_STATIC_CHUNK, 4)])
+@pytest.mark.parametrize("n,cols", [(1, 1000), (100, 300), (300, 5000), (1000, 1000), (2500, 80000), (4694, 42607),
+                                    (8192, 24414), (16384, 16384), (100000, 256)])
+def test_matvec_shape_beside_the_callers(hctx, pol, chunk, n, cols):
+    args = U.upir_matvec_args(0x10000000, 0x20000000, 0x30000000, cols, cols)
+    shape = lambda spmd: resolve(hctx, U.UPIR_BODY_MATVEC, args, [(0, n, 1)], H.make_sched(pol, chunk), spmd)[1:3]
+    for teams in (1, 16, 256, 1024):
+        assert shape((teams, 0)) == (teams, 256)
+    rest = max(1, min(-(-n // 4), 2048))
+    for units in (64, 128, 256, 512, 1024):
+        T, Uu = shape((0, units))
+        assert Uu == units and T >= rest or (T, Uu) == shape((0, 0))
+    if pol != U.UPIR_SCHED_AUTO:
+        one = resolve(hctx, U.UPIR_BODY_MATVEC, args, [(0, n, 1)], H.make_sched(pol, chunk, U.UPIR_DIST_UNITS))
+        assert one[1:3] == (1, 256)
+        assert resolve(hctx, U.UPIR_BODY_MATVEC, args, [(0, n, 1)],
+                       H.make_sched(pol, chunk, U.UPIR_DIST_TEAMS))[1] >= rest
+    if chunk == 4:  # rows that are not dealt one by one: no eight-wavefront teams
+        assert shape((0, 0))[1] < 512
+
+
 @pytest.mark.gpu
 def test_matmul_tuned_choice_fits_the_units():
     torch = pytest.importorskip("torch")
