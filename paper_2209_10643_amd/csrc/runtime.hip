@@ -818,9 +818,11 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
                                    fixed->distribute == UPIR_DIST_TEAMS_UNITS);
       const int32_t rest_teams = (int32_t)std::max<int64_t>(1, std::min<int64_t>(cdiv(n, 4), cap));
       sp.num_teams = rest_teams;
-      if (!lp->has_red && n < 4 * cus) {
+      if (!lp->has_red && (n <= 2 * cus || (n < 4 * cus && cols >= 8192))) {
         // a wavefront per row on CUs of their own (255 x 39807: 13.3 us, 19.2
-        // four to a team; 300 x 5000: 4.9 and 5.9)
+        // four to a team; 300 x 5000: 4.3 and 4.9). Over two rows a CU short
+        // rows are better four to a team (800 x 5000: 4.9, alone 5.6; 746 x
+        // 8465: 6.9 and 6.0).
         sp.num_teams = (int32_t)std::max<int64_t>(1, n);
         sp.num_units = 64;
       } else if (!lp->has_red && n >= 8 * cus && n * cols >= (n < 32 * cus ? 48LL << 20 : 128LL << 20)) {

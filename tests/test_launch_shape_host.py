@@ -103,6 +103,12 @@ def test_matvec_shape_beside_the_callers(hctx, pol, chunk, n, cols):
         assert shape((0, 0))[1] < 512
 
 
+def test_matvec_short_rows_four_to_a_team(hctx):
+    shape = lambda n, cols: resolve(hctx, U.UPIR_BODY_MATVEC, U.upir_matvec_args(
+        0x10000000, 0x20000000, 0x30000000, cols, cols), [(0, n, 1)])[1:3]
+    assert shape(800, 5000) == (200, 256) and shape(800, 20000) == (800, 64) and shape(512, 5000) == (512, 64)
+
+
 @pytest.mark.gpu
 def test_matmul_tuned_choice_fits_the_units():
     torch = pytest.importorskip("torch")
