@@ -932,12 +932,17 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     // A team of 256 units owns or claims 256 chunks at a time. Where that
     // leaves three quarters of the CUs without a range, teams of one
     // wavefront have four times as many (AXPY, chunk 1024: 27 us against 37
-    // for n = 5,000,003, 17 against 28 for 500,003). Not where the units'
-    // number orders a float32 sum.
+    // for n = 5,000,003, 17 against 28 for 250,003), if there are two ranges
+    // of theirs at least (chunk 16384: 392 us against 114 for 1,000,003) and
+    // a range is long beside what starting it costs (chunk 1, 16,000
+    // elements: 27 us against 9; chunk 16, 250,003: 4.3 and 3.2; chunk 64:
+    // 3.5 and 4.4). Beside the caller's teams the units stay: one wavefront
+    // to each of 16 teams took 27 us for those 16,000 elements, 9 with four.
+    // Not where the units' number orders a float32 sum.
     const bool chunked = sc.policy == UPIR_SCHED_STATIC_CHUNK || sc.policy == UPIR_SCHED_DYNAMIC;
-    if (chunked && sc.distribute == UPIR_DIST_TEAMS_UNITS && lp->loop.dim[0].step == 1 && sc.tile[0] == 0 &&
+    if (chunked && sp.num_teams == 0 && sc.distribute == UPIR_DIST_TEAMS_UNITS && lp->loop.dim[0].step == 1 && sc.tile[0] == 0 &&
         team_stream_body(lp->kind, lp->sum_dtype, lp->has_red ? lp->red.op : UPIR_RED_NONE) &&
-        sc.chunk > lp->n / (64LL * c->num_cus))
+        sc.chunk > lp->n / (64LL * c->num_cus) && sc.chunk >= 64 && sc.chunk <= lp->n / 128)
       sp.num_units = 64;
   }
   if (lp->kind == UPIR_BODY_MATVEC && (sp.num_units % 64) != 0)

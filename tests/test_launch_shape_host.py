@@ -109,6 +109,23 @@ def test_matvec_short_rows_four_to_a_team(hctx):
     assert shape(800, 5000) == (200, 256) and shape(800, 20000) == (800, 64) and shape(512, 5000) == (512, 64)
 
 
+@pytest.mark.parametrize("pol", [U.UPIR_SCHED_STATIC_CHUNK, U.UPIR_SCHED_DYNAMIC])
+def test_stream_units(hctx, pol):
+    def units(n, chunk, teams=0, red=None):
+        args = U.upir_axpy_args(2.5, 0, 0x10000000, 0x20000000)
+        r = H.make_red(red, 0x30000000) if red else None
+        return resolve(hctx, U.UPIR_BODY_AXPY, args, [(0, n, 1)], H.make_sched(pol, chunk), (teams, 0), r)[2]
+    for n, chunk in ((250003, 64), (250003, 1024), (5000003, 1024)):
+        assert units(n, chunk) == units(n, chunk, red=U.UPIR_RED_MAX) == 64  # few ranges, each of them long
+        assert units(n, chunk, red=U.UPIR_RED_SUM) == 256                    # the units order the sum
+        for teams in (1, 16, 256):
+            assert units(n, chunk, teams) == 256
+    for n in (1000, 16000, 65000, 250003):  # short ranges
+        for chunk in (1, 3, 4, 16):
+            assert units(n, chunk) == 256
+    assert units(1000003, 16384) == 256 and units(4000, 64) == 256  # a single range on 64 units
+
+
 @pytest.mark.gpu
 def test_matmul_tuned_choice_fits_the_units():
     torch = pytest.importorskip("torch")
