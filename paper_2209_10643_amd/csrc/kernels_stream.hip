@@ -54,16 +54,18 @@ struct TeamRanges {
 
   __device__ TeamRanges(const SchedK &S_, int64_t n_, int team_)
       : S(S_), n(n_), team(team_), nq(S_.T < 64 ? 1 : (S_.T / 32 < DYN_QUEUES ? S_.T / 32 : DYN_QUEUES)), q(team_ % nq) {
-    // chunk x U, at most n
-    const int64_t c = S.chunk < 1 ? 1 : S.chunk;
-    const int64_t cu = c > n / S.U ? (n > 0 ? n : 1) : c * S.U;
     if (S.policy == POL_STATIC) {
       int64_t hi;
       block_range(n, S.T, team, at, hi);
       len = hi - at;
       step = n + 1 - at;  // one range
       if (len <= 0) at = n;
-    } else if (S.policy == POL_CHUNK) {
+      return;
+    }
+    // chunk x U, at most n
+    const int64_t c = S.chunk < 1 ? 1 : S.chunk;
+    const int64_t cu = c > quot(n, S.U) ? (n > 0 ? n : 1) : c * S.U;
+    if (S.policy == POL_CHUNK) {
       len = cu;
       step = (int64_t)S.T * cu;
       at = (int64_t)team * cu;
@@ -195,6 +197,14 @@ __global__ void __launch_bounds__(1024) k_team_stream(int64_t n, SchedK S, RedK 
   TeamRanges ranges(S, n, blockIdx.x);
   int64_t lo, hi;
   while (ranges.next(lo, hi)) {
+    // A range of no more elements than units: one each, in one access. In
+    // vectors its ends would be accesses of their own, one after another
+    // (AXPY, 65,000 elements in 1,024 static blocks: 3.4 us, 4.4 with them;
+    // chunk 1 from element 1, 5,000,003 elements: 39 and 95).
+    if (hi - lo <= U) {
+      if (tid < hi - lo) one(lo + tid);
+      continue;
+    }
     // elements up to the first 16-byte boundary of the array that is written
     // (or read, for SUM), side by side (at most three, which a team of one or
     // two units takes in turn); x may stay unaligned beside y
