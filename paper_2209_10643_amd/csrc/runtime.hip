@@ -734,11 +734,28 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         if (th == 64) return (tiles >= 4 * cus && 16 * tiles <= 17 * 4 * cus) || tiles >= 12 * cus;
         return 2 * tiles >= 3 * cus;
       };
-      for (int th : {128, 64, 32, 16, 8})
-        if (enough(th)) {
-          sc.tile[0] = th;
-          break;
-        }
+      auto tallest = [&](auto &&ok) {
+        for (int th : {128, 64, 32, 16, 8})
+          if (ok(th)) return th;
+        return 4;
+      };
+      int th = tallest(enough);
+      // The above is for tiles of four wavefronts, one tile to a team. The
+      // rule for any shape is the tallest tile that still makes 4 x CUs of
+      // them; it holds where the caller gives the teams (2048 x 2048 with a
+      // synchronous residual on 1,024 teams: 13.4 us, by the above 17.7). On
+      // fewer wavefronts the lower of the two is better (1000 x 1000, no
+      // residual, 64 units: 4.3 us on 4 rows, 5.0 on 8; 4096 x 4096, async:
+      // 41 on 64, 25 on 16), on more the taller (4096 x 4096, async, 1,024
+      // units: 29 on 64, 61 on 16; filter of 1500 x 2004, 512: 16.8 on 8, 12.6
+      // on 16).
+      const int units = given ? given->num_units : 0;
+      if (given && (given->num_teams > 0 || (units != 0 && units != 256))) {
+        const int any = tallest([&](int h) { return (h < 128 || !filter) && cdiv(rows, h) * ct >= 4 * cus; });
+        if (given->num_teams > 0 || units % WAVE != 0) th = any;
+        else th = units < 256 ? std::min(th, any) : std::max(th, any);
+      }
+      sc.tile[0] = th;
       sp.num_teams = 0;  // one tile per team
       break;
     }

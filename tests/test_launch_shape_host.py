@@ -126,6 +126,34 @@ def test_stream_units(hctx, pol):
     assert units(1000003, 16384) == 256 and units(4000, 64) == 256  # a single range on 64 units
 
 
+@pytest.mark.parametrize("body", ["none", "sync", "async", "filter"])
+@pytest.mark.parametrize("N,M", [(34, 66), (500, 500), (1000, 1000), (1500, 2004), (2048, 2048), (3000, 3000),
+                                 (4096, 4096), (4832, 5992), (16384, 16384)])
+def test_tile_height_beside_the_callers_shape(hctx, body, N, M):
+    g = 3 if body == "filter" else 1
+    rows, ct = N - 2 * g, -(-(M - 2 * g) // 256)
+    any_shape = next((h for h in (128, 64, 32, 16, 8) if (h < 128 or body != "filter") and -(-rows // h) * ct >= 1024), 4)
+
+    def height(spmd):
+        dims = [(g, N - g, 1), (g, M - g, 1)]
+        if body == "filter":
+            args = U.upir_filter7_args(0x10000000, 0x7000000000, 0x9000, M)
+            return resolve(hctx, U.UPIR_BODY_FILTER7, args, dims, None, spmd)[3][0]
+        red = None if body == "none" else H.make_red(U.UPIR_RED_MAX, 0x9000, async_=body == "async")
+        args = U.upir_jacobi5_args(0x10000000, 0x7000000000, M)
+        return resolve(hctx, U.UPIR_BODY_JACOBI5, args, dims, None, spmd, red)[3][0]
+
+    free = height((0, 0))
+    assert height((0, 256)) == free
+    for teams in (1, 256, 1024):
+        assert height((teams, 0)) == height((teams, 256)) == any_shape
+    for units in (64, 128):
+        assert height((0, units)) == min(free, any_shape)
+    for units in (512, 1024):
+        assert height((0, units)) == max(free, any_shape)
+    assert height((0, 100)) == any_shape
+
+
 @pytest.mark.gpu
 def test_matmul_tuned_choice_fits_the_units():
     torch = pytest.importorskip("torch")
