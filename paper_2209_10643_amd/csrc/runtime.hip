@@ -787,10 +787,14 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
                                  {64, 128, 512, 1, false, 37.0}, {64, 64, 512, 1, false, 22.0}, {32, 32, 512, 1, false, 7.3}};
       static const Tile bf16[] = {{256, 256, 256, 1, true, 22.0}, {128, 128, 256, 2, true, 20.0},
                                   {128, 128, 512, 1, false, 19.0}, {64, 128, 512, 1, false, 14.0}, {64, 64, 512, 1, false, 10.5},
-                                  {32, 32, 512, 1, false, 5.0}};
+                                  {32, 32, 512, 1, false, 5.0}, {256, 256, 512, 1, true, 31.0}};
       static const Tile split[] = {{256, 256, 256, 1, true, 60.0}, {128, 128, 256, 2, true, 45.0},
                                    {128, 128, 512, 1, false, 30.0}, {64, 128, 512, 1, false, 22.0}, {64, 64, 512, 1, false, 14.0},
-                                   {32, 32, 512, 1, false, 6.0}};
+                                   {32, 32, 512, 1, false, 6.0}, {256, 256, 512, 1, true, 75.0}};
+      // the last tile of the two lists, the eight-wavefront 256 x 256, is only
+      // for 512 units that the caller gives (4096^3 in bfloat16: 164 us, 128 x
+      // 128 on 512 units 315, 256 x 256 on 256 units 126) and for a named tile
+      // that is too large for the other's 32-bit offsets
       const bool is_f32 = lp->kind == UPIR_BODY_MATMUL_F32, is_split = lp->kind == UPIR_BODY_MATMUL_SPLIT3;
       const Tile *tiles = is_f32 ? f32 : is_split ? split : bf16;
       const int64_t M = lp->cnt[0], N = lp->cnt[1], K = ((const upir_matmul_args *)lp->args)->K;
@@ -801,18 +805,19 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // names, the units; without one that fits, neither does.
       const int32_t units = given ? given->num_units : 0;
       const bool named = fixed && fixed->policy != UPIR_SCHED_AUTO && fixed->tile[0] > 0;
-      bool fits = false;
-      for (int i = 0; i < (is_f32 ? 5 : 6); ++i)
-        fits = fits || ((!units || tiles[i].units == units) &&
-                        (!named || (tiles[i].bm == fixed->tile[0] && tiles[i].bn == fixed->tile[1])));
+      const int ntiles = is_f32 ? 5 : (units == 512 || named) ? 7 : 6;
+      auto suits = [&](const Tile &t) {
+        return (!units || t.units == units) && (!named || (t.bm == fixed->tile[0] && t.bn == fixed->tile[1]));
+      };
+      const bool fits = std::any_of(tiles, tiles + ntiles, suits);
       sc.policy = UPIR_SCHED_STATIC;
       sp.num_teams = 0;
       double best = 0.0;
-      for (int i = 0; i < (is_f32 ? 5 : 6); ++i) {
+      for (int i = 0; i < ntiles; ++i) {
         const Tile &t = tiles[i];
-        if (fits && ((units && t.units != units) || (named && (t.bm != fixed->tile[0] || t.bn != fixed->tile[1])))) continue;
-        // the 256 x 256 tile addresses each operand with 32-bit offsets
-        if (t.pre && t.bm == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;
+        if (fits && !suits(t)) continue;
+        // the four-wavefront 256 x 256 tile addresses each operand with 32-bit offsets
+        if (t.pre && t.bm == 256 && t.units == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;
         int64_t at_once = (int64_t)t.per * c->num_cus;
         if (given && given->num_teams > 0) at_once = std::min<int64_t>(at_once, given->num_teams);
         double us = 1e-3 * t.ns * (double)K * (double)cdiv(cdiv(M, t.bm) * cdiv(N, t.bn), at_once);

@@ -69,6 +69,17 @@ def test_matmul_tile_for_few_teams(hctx):
     assert matmul(hctx, "f32", 512, 512, 512)[3] == (32, 32)
 
 
+@pytest.mark.parametrize("kind", ["bf16", "split"])
+def test_matmul_large_tile_on_512_units(hctx, kind):
+    for n in (3000, 4096, 8192):
+        assert matmul(hctx, kind, n, n, n, None, (0, 512)) == ("matmul_mfma", (-(-n // 256)) ** 2, 512, (256, 256))
+        assert matmul(hctx, kind, n, n, n)[2:] == (256, (256, 256))
+    # operands over 2 GiB: a named 256 x 256 tile runs on the 512 units that address them, the default is another tile
+    big = matmul(hctx, kind, 70000, 512, 16384, H.make_sched(U.UPIR_SCHED_STATIC, tile=(256, 256)))
+    assert big[0] == "matmul_mfma" and big[2] == 512
+    assert matmul(hctx, kind, 70000, 512, 16384)[3] == (128, 128)
+
+
 @pytest.mark.parametrize("kind,tile,units", [
     ("f32", (256, 128), {512}), ("f32", (128, 128), {256}), ("f32", (64, 128), {512}), ("f32", (64, 64), {512}),
     ("f32", (32, 32), {512})] + [(k, t, u) for k in ("bf16", "split") for t, u in (
