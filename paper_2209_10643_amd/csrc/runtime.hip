@@ -705,9 +705,12 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // with one that is folded later, taller strips only lengthen each
       // wavefront's chain (4096 x 4096 without: 21.1 us on 16 rows, 23.0 on
       // 64; async: 23.5 and 23.4; 4833 x 5992 async: 36.0, 38.0 on 32, 40.1
-      // on 64; 8192 x 8192: 89 on 16, 98 on 128), until the partials, one per
-      // wavefront, are too many for one workgroup's fold: 32 rows from 64 x
-      // CUs tiles on. A synchronous residual pays for every workgroup (the
+      // on 64; 8192 x 8192: 89 on 16, 98 on 128; 32 rows from 16,384 tiles on).
+      // The partials of an async residual, one per wavefront, then have to fit the fold buffers that every context starts
+      // with: beyond 16,384 tiles of 32 rows its tiles are 128 high (16384 x
+      // 16384: 413 us; 402 on 32, 433 on 64), so that no grid asks for more
+      // memory, or for buffers to grow in a capture, than with 128 rows
+      // throughout. A synchronous residual pays for every workgroup (the
       // last one reads a value from each): 64 rows where the tiles fill the
       // 4 x CUs resident ones once, or often enough that the last round does
       // not count (4096 x 4096: 27.9 us, 29.0 on 32; 4833 x 5992, 1.8
@@ -727,7 +730,8 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         const int64_t tiles = cdiv(rows, th) * ct;
         if (filter) return th <= 32 && tiles >= (th == 32 ? 4 : 2) * cus;
         if (!lp->has_red || lp->red.async) {
-          if (th > 32 || (th == 32 && cdiv(rows, 16) * ct <= 64 * cus)) return false;
+          if (th == 64 || (th == 128 && !lp->has_red)) return false;
+          if (th > 16 && 4 * cdiv(rows, th == 32 ? 16 : 32) * ct <= FOLD_PARTIALS) return false;
           return 2 * tiles >= 3 * cus;
         }
         if (th == 128) return tiles >= 8 * cus;
@@ -1119,9 +1123,7 @@ upir_status settle(upir_ctx *c) {
 static upir_status ensure_fold_bufs(upir_ctx *c, int64_t parts) {
   if (parts <= c->fold_cap) return UPIR_OK;
   if (c->capturing) return upir_fail(c, UPIR_ESTATE, "fold buffers must grow; launch once before capturing");
-  // room for every default launch up to grids of 32768 x 32768, so that a
-  // capture finds it whatever async loop ran first
-  const int64_t cap = std::max<int64_t>(parts, 1 << 20);
+  const int64_t cap = std::max<int64_t>(parts, FOLD_PARTIALS);
   unsigned long long *nb[2];
   for (int i = 0; i < 2; ++i) {
     nb[i] = (unsigned long long *)upir_dalloc(c, (size_t)cap * 8);

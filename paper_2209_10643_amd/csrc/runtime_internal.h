@@ -29,6 +29,8 @@ struct Mapping {
 //   [1280] reduction slots, one 128-byte line per workgroup (value, flag)
 constexpr size_t SCR_RESULT = 8, SCR_DYNEXIT = 24, SCR_DYN = 256;
 constexpr size_t SCR_SLOTS = SCR_DYN + upir::DYN_QUEUES * 8 * upir::SLOT_WORDS;
+// Partials that a context's fold buffers hold from their first use on.
+constexpr int64_t FOLD_PARTIALS = 1 << 16;
 inline size_t scratch_bytes(int64_t cap) { return SCR_SLOTS + (size_t)cap * 8 * upir::SLOT_WORDS; }
 
 struct upir_loop_obj {

@@ -165,6 +165,50 @@ def test_tile_height_beside_the_callers_shape(hctx, body, N, M):
     assert height((0, 100)) == any_shape
 
 
+@pytest.mark.parametrize("N,M", [(4096, 4096), (8192, 8192), (8300, 8300), (11600, 11600), (16384, 16384),
+                                 (23000, 23000), (600000, 12), (12, 600000), (1200000, 300)])
+def test_async_partials_fit_the_first_fold_buffers(hctx, N, M):
+    # one partial per wavefront; the buffers hold 65,536, or what a tiling of 128 rows throughout would need
+    tiles = -(-(N - 2) // 128) * -(-(M - 2) // 256)
+    red = H.make_red(U.UPIR_RED_MAX, 0x9000, async_=True)
+    args = U.upir_jacobi5_args(0x10000000, 0x7000000000, M)
+    _, T, Uu, _ = resolve(hctx, U.UPIR_BODY_JACOBI5, args, [(1, N - 1, 1), (1, M - 1, 1)], None, (0, 0), red)
+    assert T * Uu // 64 <= max(65536, 4 * tiles)
+
+
+@pytest.mark.gpu
+def test_async_memory():
+    # what the first async reduction of a context asks the allocator for
+    torch = pytest.importorskip("torch")
+    sizes = []
+
+    @U.ALLOC_FN
+    def alloc(n, user):
+        sizes.append(n)
+        return torch.cuda.caching_allocator_alloc(n)
+
+    @U.FREE_FN
+    def free(p, user):
+        torch.cuda.caching_allocator_delete(p)
+
+    h = C.c_void_p()
+    x = torch.rand(1000, device="cuda")
+    r = torch.zeros(1, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    U.upir_init(0, None, C.byref(h))
+    U.upir_set_allocator(h, alloc, free, None)
+    args = U.upir_sum_args(x.data_ptr(), U.UPIR_DT_F32, 0)
+    body = U.upir_body(U.UPIR_BODY_SUM, 1, C.cast(C.pointer(args), C.c_void_p), C.sizeof(args))
+    L, lp, red = H.make_loop([(0, 1000, 1)]), C.c_void_p(), H.make_red(U.UPIR_RED_MAX, r.data_ptr(), async_=True)
+    U.upir_loop_parallel(h, C.byref(L), None, C.byref(body), C.byref(red), C.byref(lp))
+    made = sum(sizes)
+    U.upir_spmd_launch(h, None, (C.c_void_p * 1)(lp.value), 1)
+    U.upir_sync(h)
+    assert r.item() == float(x.max())
+    assert sum(sizes) - made <= 2 * 65536 * 8
+    U.upir_finalize(h)
+
+
 @pytest.mark.gpu
 def test_matmul_tuned_choice_fits_the_units():
     torch = pytest.importorskip("torch")
