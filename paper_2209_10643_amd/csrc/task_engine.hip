@@ -488,6 +488,14 @@ __global__ void __launch_bounds__(256) k_engine(EngineD E) {
     run_tile(d, k, acc);
     item = 0;
     if (threadIdx.x == 0 && q + E.nq * claim < E.total_tiles) item = ld_u64(&E.work[q + E.nq * claim]);  // there already?
+    // Before the tile counts as done, every wavefront has run its part of it:
+    // the task's stamp marks the end of its work, and a successor, ordered by
+    // an address or by data, starts after it (the barrier, or those of the
+    // reduction). A task whose data another task touches has every thread's
+    // stores at the coherent level by then; otherwise only the reduction
+    // partial (thread 0's store) must have landed: no other task reads the
+    // data, and the kernel's end publishes it.
+    if (d.mem == MEM_COHERENT) complete_own_accesses();
     double partial = 0.0;
     if (d.red_op) {
       partial = (double)block_reduce(d.red_op, acc, s_red);  // in thread 0
@@ -495,13 +503,7 @@ __global__ void __launch_bounds__(256) k_engine(EngineD E) {
         coh_store((unsigned long long *)&E.partials[d.part_base + k], __builtin_bit_cast(unsigned long long, partial));
         complete_own_accesses();
       }
-    }
-    // Before the tile counts as done: a task whose data another task touches
-    // has every thread's tile stores at the coherent level; otherwise only
-    // the reduction partial (thread 0's store) must have landed: no other
-    // task reads the data, and the kernel's end publishes it.
-    if (d.mem == MEM_COHERENT) {
-      complete_own_accesses();
+    } else {
       __syncthreads();
     }
     if (threadIdx.x < WAVE) {
