@@ -202,8 +202,7 @@ bool filter7_tile_supports(const Filter7P &p, const LoopK &L, const SchedK &S) {
 
 hipError_t launch_filter7_tile(const Filter7P &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
   const size_t lds = (size_t)(S.tile[0] + 6) * F7_PITCH * 4;
-  static const hipError_t e = hipFuncSetAttribute((const void *)k_filter7_tile,
-                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (64 + 6) * F7_PITCH * 4);
+  const hipError_t e = raise_lds<k_filter7_tile>((64 + 6) * F7_PITCH * 4);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_filter7_tile, dim3(S.T), dim3(S.U), lds, st, L, S, p, R);
   return hipGetLastError();

@@ -73,9 +73,7 @@ __device__ inline void for_team_tiles(const SchedK &S, F &&f) {
 
 template <auto K>
 static hipError_t go_mm(const MatmulP &p, const SchedK &S, size_t lds, hipStream_t st) {
-  // raise the dynamic LDS limit once per kernel
-  static const hipError_t e =
-      hipFuncSetAttribute((const void *)K, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  const hipError_t e = raise_lds<K>(lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(K, dim3(S.T), dim3(S.U), lds, st, p, S);
   return hipGetLastError();

@@ -3,9 +3,20 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "once_per_device.h"
 #include "upir_kern.h"
 
 namespace upir {
+
+// Raises kernel K's limit of dynamic LDS to `lds` bytes on the current device.
+template <auto K>
+inline hipError_t raise_lds(size_t lds) {
+  static OncePerDevice once;
+  int dev = -1;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  return once.run(dev, [&] { return hipFuncSetAttribute((const void *)K, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); });
+}
 
 // Kernel variants a loop can run with (reported by upir_loop_resolve).
 enum Variant : int32_t {
