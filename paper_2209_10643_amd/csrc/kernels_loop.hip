@@ -628,7 +628,7 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   // start at once, last (128-row tiles on 512 units: 24.3 us, first 24.8).
   const bool xwg = jacobi_extra_wg(R), combine = RED && !R.defer;
   const int G = xwg ? gridDim.x - 1 : gridDim.x;
-  const bool first = xwg && !combine && (int64_t)G * NW > 16 * 256;
+  const bool first = xwg && !combine && R.fold_first;
   const int wg = (int)blockIdx.x - (first ? 1 : 0);
   if (xwg && wg == (first ? -1 : G)) {
     if (R.fold.count > 0) run_fold(R.fold);

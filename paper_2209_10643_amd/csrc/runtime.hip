@@ -1169,6 +1169,7 @@ upir_status launch_plan(upir_ctx *c, upir_loop_obj *lp, const Plan &pl, bool for
   if (c->pend.on) {  // the previous async loop's fold rides on this kernel
     if (takes_fold(pl.variant) && !(lp->n == 0 && !lp->has_red)) {
       R.fold = c->pend.F;
+      R.fold_first = nparts > 16LL * c->num_cus;  // more wavefronts than start at once (k_jacobi_tile)
     } else {
       st = settle(c);
       if (st) return st;

@@ -67,6 +67,7 @@ struct RedK {
   long long spin_limit;       // bound on the combiner's wait per slot
   unsigned long long *defer;  // non-null: leave one partial per wavefront here, fold later
   FoldK fold;                 // an earlier loop's deferred fold, run by one workgroup
+  int32_t fold_first;         // Jacobi tiles: that workgroup is launched first, not last
 };
 
 // Empty float slot: all ones, a NaN that neither arithmetic nor a float32 to
