@@ -7,8 +7,9 @@
 // Two kinds of kernels:
 //  * k_generic<Body>: executes exactly the iterations each (team, unit) owns
 //    under any static / static-chunk / tiled schedule, any distribute and
-//    collapse 1..3, decoding induction values as it goes. Correct for every
-//    body, used for anything the fast kernels do not cover.
+//    collapse 1..3, decoding induction values as it goes (k_dynamic: under
+//    dynamic and guided claims). Correct for every body, used for anything
+//    the fast kernels do not cover; launch_generic decides.
 //  * fast kernels that own the same iterations with wide, coalesced access:
 //    k_stream4 (1-D, chunk 4: one f32x4 per chunk, chunks dealt over the
 //    flat unit id -- the classic grid-stride loop), k_jacobi_tile (tiles of
@@ -426,18 +427,19 @@ constexpr int JT_W = 256;  // tile width (points)
 // Residual reduction. The float64 value of |u1 - u0| is only needed where it
 // can change the maximum (or minimum): rounding to float32 is monotonic, so a
 // point whose float32 |u1 - u0| is below a maximum already found cannot hold
-// the exact one. Each lane has a threshold of its own, its best so far, and in
-// a strip of at most four rows (the default shape of a deferred residual) also
-// the wavefront's best of the first row: 23.4 us a sweep of 4096 x 4096, with
-// the lanes' own alone 24.2. In longer strips the lanes' own do as well, and
-// on a smooth grid, whose updates grow along a strip, sharing the wavefront's
-// after every hit cost 1 to 3%. Only candidates at or above the threshold take
-// the float64 path; the result is exact.
-template <int OP>
+// the exact one. Each lane has a threshold of its own, its best so far. SHARE,
+// for strips of at most four rows (the default shape of a deferred residual):
+// also the wavefront's best of the first row: 23.4 us a sweep of 4096 x 4096,
+// with the lanes' own alone 24.2. In longer strips the lanes' own do as well,
+// and the test whether to share, taken at every row, cost them 1.5 to 2.5%
+// (64-row tiles on 256 units: 25.1 us with it, 24.7 without). Only
+// candidates at or above the threshold take the float64 path; the result is
+// exact.
+template <int OP, bool SHARE>
 struct ResidualAcc {
   float m32 = OP == RED_MIN ? __builtin_inff() : -1.0f;  // this lane's best candidate, in float32
-  float w32 = m32;                                       // below (above) it no point of this lane can matter
-  bool share = false;                                    // the wavefront's best is still to be shared
+  float w32 = m32;                                       // SHARE: below (above) it no point of this lane can matter
+  bool share = SHARE;                                    // the wavefront's best is still to be shared
   double m64 = OP == RED_SUM ? 0.0 : (OP == RED_MAX ? -__builtin_inf() : __builtin_inf());
   __device__ void add(float v, float c) {
     if (OP == RED_SUM) {
@@ -477,6 +479,11 @@ struct ResidualAcc {
     const float d0 = mk & 1 ? fabsf(v.x - c.x) : NONE, d1 = mk & 2 ? fabsf(v.y - c.y) : NONE;
     const float d2 = mk & 4 ? fabsf(v.z - c.z) : NONE, d3 = mk & 8 ? fabsf(v.w - c.w) : NONE;
     const float dm = OP == RED_MAX ? fmaxf(fmaxf(d0, d1), fmaxf(d2, d3)) : fminf(fminf(d0, d1), fminf(d2, d3));
+    if constexpr (!SHARE) {
+      if (OP == RED_MAX ? dm < m32 : dm > m32) return;
+      points(v, c, mk);
+      return;
+    }
     if (OP == RED_MAX ? dm >= w32 : dm <= w32) {
       points(v, c, mk);
       w32 = OP == RED_MAX ? fmaxf(w32, m32) : fminf(w32, m32);
@@ -507,9 +514,9 @@ struct ResidualAcc {
 // columns [clo, chi] that in-box points read and write only [wlo, whi); a
 // lane whose four columns straddle a read bound loads them one by one. Byte
 // offsets within a strip fit 32 bits (checked when the variant is chosen).
-template <bool EDGE, int RED, bool NT>
+template <bool EDGE, int RED, bool NT, bool SHARE>
 __device__ __forceinline__ void jacobi_strip(const float *sp, float *dp, int ld, int n, int lane, int clo, int chi,
-                                             int wlo, int whi, ResidualAcc<RED> &acc) {
+                                             int wlo, int whi, ResidualAcc<RED, SHARE> &acc) {
   constexpr uint32_t OFF = 0x80000000u;  // past the extent: reads as zero
   // rows per load group: 4 without a residual, 2 with one (the residual's
   // registers and arithmetic leave room for fewer rows in flight)
@@ -613,7 +620,7 @@ __device__ __forceinline__ void jacobi_strip(const float *sp, float *dp, int ld,
 // NT: the grids exceed the last-level cache, so the new grid is stored with
 // the non-temporal hint (a grid that fits is read back from that cache by the
 // next sweep and is stored normally).
-template <int RED, bool NT>
+template <int RED, bool NT, bool SHARE>
 __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP p, RedK R) {
   const int TH = S.tile[0];
   const int lane = threadIdx.x % WAVE;
@@ -632,7 +639,7 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   const int wg = (int)blockIdx.x - (first ? 1 : 0);
   if (xwg && wg == (first ? -1 : G)) {
     if (R.fold.count > 0) run_fold(R.fold);
-    if (combine) finish_reduction<double>(R, ResidualAcc<RED>().m64);
+    if (combine) finish_reduction<double>(R, ResidualAcc<RED, SHARE>().m64);
     return;
   }
   const int team = xcd_team(wg, G);
@@ -640,8 +647,7 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
   const int64_t ilo = L.lb[0], ihi = L.lb[0] + L.cnt[0];  // interior rows [ilo, ihi)
   const int64_t jlo = L.lb[1], jhi = L.lb[1] + L.cnt[1];
   const int ld = (int)p.ld;
-  ResidualAcc<RED> acc;
-  acc.share = SH <= 4;
+  ResidualAcc<RED, SHARE> acc;
 
   auto do_tile = [&](int64_t m) {
     const int64_t mi = quot(m, S.nt[1]), ti = S.t0[0] + mi, tj = S.t0[1] + (m - mi * S.nt[1]);
@@ -653,11 +659,11 @@ __global__ void __launch_bounds__(1024) k_jacobi_tile(LoopK L, SchedK S, JacobiP
     float *dp = p.dst + ra * p.ld + j0;
     const int n = (int)(rb - ra);
     if (j0 >= jlo && j0 + JT_W <= jhi) {
-      jacobi_strip<false, RED, NT>(sp, dp, ld, n, lane, -1, JT_W, 0, JT_W, acc);
+      jacobi_strip<false, RED, NT, SHARE>(sp, dp, ld, n, lane, -1, JT_W, 0, JT_W, acc);
     } else {
       // tile columns read by in-box points (inclusive) and written (half-open)
       const int wlo = (int)((j0 > jlo ? j0 : jlo) - j0), whi = (int)((j0 + JT_W < jhi ? j0 + JT_W : jhi) - j0);
-      jacobi_strip<true, RED, NT>(sp, dp, ld, n, lane, wlo - 1, whi, wlo, whi, acc);
+      jacobi_strip<true, RED, NT, SHARE>(sp, dp, ld, n, lane, wlo - 1, whi, wlo, whi, acc);
     }
   };
 
@@ -696,16 +702,28 @@ bool jacobi_tile_supports(const JacobiP &p, const LoopK &L, const SchedK &S) {
   return jacobi_strips_support(p, L, S) && (p.ld % 4) == 0 && ((uintptr_t)p.src % 16) == 0 && ((uintptr_t)p.dst % 16) == 0;
 }
 
+template <int RED, bool NT>
+static hipError_t go_jacobi_red(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
+  const dim3 g(S.T + (jacobi_extra_wg(R) ? 1 : 0)), b(S.U);
+  const int waves = S.U / WAVE, strip = (S.tile[0] + waves - 1) / waves;
+  if constexpr (RED == RED_MAX || RED == RED_MIN) {
+    if (strip <= 4) {
+      hipLaunchKernelGGL((k_jacobi_tile<RED, NT, true>), g, b, 0, st, L, S, p, R);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_jacobi_tile<RED, NT, false>), g, b, 0, st, L, S, p, R);
+  return hipGetLastError();
+}
+
 template <bool NT>
 static hipError_t go_jacobi(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
-  const dim3 g(S.T + (jacobi_extra_wg(R) ? 1 : 0)), b(S.U);
   switch (R.op) {
-    case RED_NONE: hipLaunchKernelGGL((k_jacobi_tile<RED_NONE, NT>), g, b, 0, st, L, S, p, R); break;
-    case RED_SUM: hipLaunchKernelGGL((k_jacobi_tile<RED_SUM, NT>), g, b, 0, st, L, S, p, R); break;
-    case RED_MAX: hipLaunchKernelGGL((k_jacobi_tile<RED_MAX, NT>), g, b, 0, st, L, S, p, R); break;
-    default: hipLaunchKernelGGL((k_jacobi_tile<RED_MIN, NT>), g, b, 0, st, L, S, p, R); break;
+    case RED_NONE: return go_jacobi_red<RED_NONE, NT>(p, L, S, R, st);
+    case RED_SUM: return go_jacobi_red<RED_SUM, NT>(p, L, S, R, st);
+    case RED_MAX: return go_jacobi_red<RED_MAX, NT>(p, L, S, R, st);
+    default: return go_jacobi_red<RED_MIN, NT>(p, L, S, R, st);
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_jacobi_tile(const JacobiP &p, const LoopK &L, const SchedK &S, const RedK &R, hipStream_t st) {
