@@ -72,11 +72,11 @@ class Timer:
 # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (scales from a 1 GiB copy), bytes,
 # from profiles/jacobi5_4096_hbm_traffic.md (re-taken whenever the kernel changes).
 JACOBI_4096_TRAFFIC = {
-    (8, 64): 143890192, (8, 128): 135156624, (8, 256): 135218826, (8, 512): 135693600,
-    (16, 64): 143543925, (16, 128): 141761173, (16, 256): 135000416, (16, 512): 135172896,
-    (32, 64): 139317050, (32, 128): 143373477, (32, 256): 142459741, (32, 512): 134985744,
-    (64, 64): 136936149, (64, 128): 139121904, (64, 256): 143289009, (64, 512): 140515427,
-    (128, 64): 135991989, (128, 128): 136956768, (128, 256): 139148192, (128, 512): 143243109,
+    (8, 64): 143722762, (8, 128): 135215749, (8, 256): 135236917, (8, 512): 135729738,
+    (16, 64): 143554757, (16, 128): 142737300, (16, 256): 135093019, (16, 512): 135237834,
+    (32, 64): 139309994, (32, 128): 143361797, (32, 256): 143251648, (32, 512): 135053797,
+    (64, 64): 136990378, (64, 128): 139255824, (64, 256): 143353637, (64, 512): 140751914,
+    (128, 64): 136045440, (128, 128): 136986544, (128, 256): 139179936, (128, 512): 143301189,
 }
 
 

@@ -273,7 +273,9 @@ upir_status upir_reduce(upir_ctx *ctx, int32_t op, int32_t dtype, const void *de
 upir_status upir_reduce_noalloc(upir_ctx *ctx, int32_t op, int32_t dtype, const void *dev_in, int64_t n,
                                 const upir_spmd *spmd, const upir_sched *sched, upir_reduction *red);
 /* The launch geometry and kernel variant the library would use (after AUTO
- * resolution): teams, units and the resolved schedule. */
+ * resolution): teams, units and the resolved schedule. Tiled Jacobi, filter
+ * and float32 matmul loops whose operands or pitches are not multiples of 16
+ * bytes report the generic variant although the same tile kernels run them. */
 upir_status upir_loop_resolve(upir_ctx *ctx, const upir_spmd *spmd, upir_loop_h loop,
                               upir_spmd *spmd_out, upir_sched *sched_out, int32_t *variant_out);
 /* Bytes of BF16 workspace a MATMUL_BF16 / MATMUL_SPLIT3 body needs:

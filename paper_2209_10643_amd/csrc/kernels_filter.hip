@@ -27,7 +27,7 @@ typedef const __attribute__((address_space(4))) float const_float;  // read thro
 // move between the multiply-adds. The former kernel kept the weights and
 // seven rotating output rows in vector registers, passed columns between
 // lanes and waited for memory once per four input rows: 19.7 us for 2048 x
-// 2048 and 9 us for any small grid, against 12.2 and 5 here (8192 x 8192: 156
+// 2048 and 9 us for any small grid, against 13.0 and 5 here (8192 x 8192: 156
 // and 136).
 constexpr int F7_W = 256;            // tile width (points)
 constexpr int F7_PITCH = F7_W + 8;   // floats per LDS row: columns -3 .. 260 of the tile

@@ -184,19 +184,20 @@ hipError_t launch_bf16_split(const MatmulP &p, bool need_lo, hipStream_t st) {
 // within-tile assignment of points to units is fixed by the matrix cores.
 //
 // Waves form a WM x WN grid; each wave owns (BM/WM) x (BN/WN) of the tile as
-// 32 x 32 MFMA blocks. K advances in steps of BK. In the tiles below
-// (k_mm_bf16, k_mm_f32) the next step's operands are fetched from global
-// memory into registers while the current step's operands, staged in LDS
-// (padded or swizzled rows: no bank conflicts on the fragment reads), feed
-// the matrix cores; the four-wave 256 x 256 tile further down
-// (k_mm_bf16_wide) loads straight into a ring of LDS stages instead.
+// 32 x 32 MFMA blocks. K advances in steps of BK. In k_mm_bf16
+// the next step's operands are fetched from global memory into registers
+// while the current step's operands, staged in LDS (padded or swizzled rows:
+// no bank conflicts on the fragment reads), feed the matrix cores; the
+// four-wave 256 x 256 tile further down (k_mm_bf16_wide) loads straight into
+// a ring of LDS stages instead. The tiles that read float32 operands
+// themselves are in kernels_matmul_direct.hip (bfloat16, split) and
+// kernels_matmul_f32.hip.
 //
 // bfloat16 variants use v_mfma_f32_32x32x16_bf16 (lane l supplies row l%32
 // and 8 consecutive k of group l/32); both hi/lo operands come from the
 // pre-pass workspace (A as M x K, B transposed as N x K, or k-panels of 32
 // for the wide tile). The split variant accumulates lo_A hi_B, hi_A lo_B and
-// hi_A hi_B into one float32 sum. float32 uses v_mfma_f32_32x32x2f32 over A
-// (M x K) and B (K x N) directly.
+// hi_A hi_B into one float32 sum.
 // The same stores with the non-temporal hint (C is written once and not read
 // again here); the row and column tests are hoisted out of the element loop,
 // and left out for tiles known to be whole (CHECK false: each test became a

@@ -13,7 +13,8 @@
 //    microseconds) from 32 features of (loop, candidate). It is trained on
 //    the timing table by this file's own kernels: one over the rows (forward
 //    and backward, each wavefront summing its rows' gradients), one over the
-//    parameters (sum over the wavefronts, Adam).
+//    parameters (sum over the wavefronts, Adam); forward passes of very many
+//    rows have one of their own.
 #include <math.h>
 #include <stdio.h>
 #include <string.h>

@@ -3,7 +3,7 @@
 // harnesses that forbid hipMalloc).
 //
 // Its kernels are those of upir_reduce; the reduction scratch they need (a
-// 256-byte header with the dynamic-schedule counters, then one 128-byte
+// 1280-byte header with the dynamic-schedule counters, then one 128-byte
 // combine slot per workgroup) lives in one file-scope device array per GPU,
 // sized for UPIR_REDUCE_NOALLOC_MAX_TEAMS workgroups. Host code never passes
 // the array's name to a kernel or a copy: the array's device address is

@@ -714,12 +714,12 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // last one reads a value from each): 64 rows where the tiles fill the
       // 4 x CUs resident ones once, or often enough that the last round does
       // not count (4096 x 4096: 27.9 us, 29.0 on 32; 4833 x 5992, 1.8
-      // rounds, 44.5 against 42.0), and 128 where the grids leave the
-      // last-level cache. The filter brings six more rows per tile into
+      // rounds, 44.5 against 42.0; the window of 6% for "once" rests on the
+      // one size), and 128 where the grids leave the last-level cache. The filter brings six more rows per tile into
       // LDS and takes 2 x CUs tiles (1024 x 1024: 6.6 us on 8 rows, 7.4 on 4;
       // 1001 x 1501: 8.0 on 8, 8.7 on 16, 10.3 on 4), 32 rows from 4 x CUs
-      // tiles on (2048 x 2048: 12.2 us on 16, 12.4 on 32; 8192 x 8192: 136 on
-      // 32, 146 on 16, 150 on 64).
+      // tiles on (2048 x 2048: 13.6 us on 16, 13.9 on 32, in one graph of them;
+      // 8192 x 8192: 136 on 32, 146 on 16, 150 on 64).
       sc.policy = UPIR_SCHED_STATIC;
       sc.tile[1] = 256;
       sc.tile[0] = 4;

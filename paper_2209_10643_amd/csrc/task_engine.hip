@@ -123,10 +123,9 @@ __device__ inline float2 ld2(const float *p) {
 // 16-byte accesses through a buffer resource over one tile's range (the
 // resource's record count also bounds the accesses to the tile). A tile is
 // run by the whole workgroup, so base and size are the same in every lane;
-// the task descriptor they come from is read with vector loads, though, and
-// the compiler would wrap every access through a resource it cannot prove
-// uniform in a per-lane loop. Taking both from the first active lane makes
-// the resource scalar.
+// taking both from the first active lane makes that plain to the compiler,
+// which would wrap every access through a resource that it cannot prove
+// uniform in a per-lane loop.
 __device__ inline __amdgpu_buffer_rsrc_t tile_rsrc(const void *base, int64_t bytes) {
   const uint64_t b = (uint64_t)base;
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
@@ -242,7 +241,8 @@ __device__ inline void run_tile_op(const TaskD &t, int64_t tile, float &acc) {
     }
     return;
   }
-  if (t.vec) {  // unit step, 16-byte aligned start of every tile
+  // unit step; a tile with a reduction or counters starts on 16 bytes, AXPY without one at any element
+  if (t.vec) {
     const int64_t b = t.lb + lo;
     const int64_t len = hi - lo, nc = len >> 2;
     int64_t m = tid;

@@ -18,14 +18,20 @@ inline hipError_t raise_lds(size_t lds) {
   return once.run(dev, [&] { return hipFuncSetAttribute((const void *)K, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); });
 }
 
-// Kernel variants a loop can run with (reported by upir_loop_resolve).
+// Kernel variants a loop can run with, as upir_loop_resolve reports them. The
+// tiled ones are reported for operands on 16-byte boundaries and rows of whole
+// 16 bytes. V_GENERIC and V_DYNAMIC say that launch_generic chooses: tiles of
+// the same schedules whose operands are not so aligned run the same strip,
+// filter and float32 matrix kernels, AXPY and SUM under any policy but the
+// chunk-4 stream's the team streams, and everything else the schedule-exact
+// kernels.
 enum Variant : int32_t {
-  V_GENERIC = 0,      // schedule-exact generic worksharing kernel
+  V_GENERIC = 0,      // chosen by launch_generic
   V_STREAM4 = 1,      // 1-D, static chunk 4, vectorised (AXPY, SUM f32, COVER)
   V_JACOBI_TILE = 2,  // tiled Jacobi, wavefront strips
   V_MATVEC_WAVE = 3,  // one wavefront per row
   V_MATMUL_MFMA = 4,  // MFMA tiles over C
-  V_DYNAMIC = 5,      // dynamic / guided claim loop (generic bodies)
+  V_DYNAMIC = 5,      // dynamic / guided claims, chosen by launch_generic
   V_FILTER7_TILE = 6, // tiled 7 x 7 filter, wavefront strips
 };
 
