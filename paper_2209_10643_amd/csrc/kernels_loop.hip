@@ -143,21 +143,21 @@ __global__ void __launch_bounds__(1024) k_dynamic(LoopK L, SchedK S, RedK R, B b
   A acc = red_identity<A>(R.op ? R.op : RED_SUM);
   auto f = [&](int64_t k, const int64_t *iv) { body(k, iv, team, unit, acc, R.op); };
   const long long n = L.n;
+  // a claim of every team past the end must still fit the counter: no claim is longer than the loop
+  const long long least = claim_length(n, S.chunk, S.U);
   for (;;) {
     if (threadIdx.x == 0) {
       long long lo, hi;
       if (S.policy == POL_DYNAMIC) {
-        long long len = S.chunk * (long long)S.U;
-        lo = atomicAdd((unsigned long long *)S.dyn_next, (unsigned long long)len);
-        hi = lo + len < n ? lo + len : n;
+        lo = atomicAdd((unsigned long long *)S.dyn_next, (unsigned long long)least);
+        hi = lo + least < n ? lo + least : n;
       } else {  // guided: claim max(chunk*U, remaining / (2T))
         long long cur = __hip_atomic_load(S.dyn_next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         for (;;) {
           if (cur >= n) { lo = hi = n; break; }
           long long rem = n - cur;
           long long len = rem / (2LL * S.T);
-          long long mn = S.chunk * (long long)S.U;
-          if (len < mn) len = mn;
+          if (len < least) len = least;
           long long want = cur + len < n ? cur + len : n;
           if (__hip_atomic_compare_exchange_strong(S.dyn_next, &cur, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_AGENT)) {

@@ -1002,6 +1002,8 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
       }
     }
   }
+  S.chunk = bounded_chunk(S.chunk, S.tiled ? S.ntiles : L.n);
+  S.nchunks = chunk_count(L.n, S.chunk > 0 ? S.chunk : 1);
   int64_t T = sp.num_teams;
   if (S.dist == UPIR_DIST_UNITS) {
     if (T > 1) return upir_fail(c, UPIR_EINVAL, "distribute(units) runs on one team");
@@ -1043,7 +1045,7 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
   } else if ((lp->kind == UPIR_BODY_AXPY || lp->kind == UPIR_BODY_COVER ||
               (lp->kind == UPIR_BODY_SUM && lp->sum_dtype == UPIR_DT_F32)) &&
              !S.tiled && S.dist == UPIR_DIST_TEAMS_UNITS && L.nd == 1 && L.step[0] == 1 &&
-             ((S.policy == UPIR_SCHED_STATIC_CHUNK && S.chunk == 4) ||
+             ((S.policy == UPIR_SCHED_STATIC_CHUNK && sc.chunk == 4) ||
               (S.policy == UPIR_SCHED_STATIC && L.n == 4LL * S.T * S.U))) {
     // COVER counts by iteration number, so its vector path starts at 0
     if (lp->kind != UPIR_BODY_COVER || L.lb[0] == 0) v = V_STREAM4;

@@ -18,6 +18,8 @@
 
 #include <type_traits>
 
+#include "chunk_math.h"
+
 namespace upir {
 
 enum : int32_t { POL_STATIC = 0, POL_CHUNK = 1, POL_DYNAMIC = 2, POL_GUIDED = 3 };
@@ -36,7 +38,8 @@ struct LoopK {
 
 struct SchedK {
   int32_t policy, dist;
-  int64_t chunk;
+  int64_t chunk;    // at most the iterations (tiles) there are
+  int64_t nchunks;  // chunks of the loop (POL_CHUNK, untiled)
   int32_t tiled;
   int32_t tile[3];
   int64_t t0[3], nt[3], ntiles;  // tile grid (tiled only)
@@ -180,7 +183,7 @@ __device__ inline void for_owned_untiled(const LoopK &L, const SchedK &S, int te
     if (tt && unit != 0) return;
     const int64_t first = tu ? (int64_t)team * S.U + unit : (tt ? (int64_t)team : (int64_t)unit);
     const int64_t stride = tu ? (int64_t)S.T * S.U : (tt ? (int64_t)S.T : (int64_t)S.U);
-    for (int64_t m = first; m * c < n; m += stride) {
+    for (int64_t m = first; m < S.nchunks; m += stride) {
       int64_t lo = m * c, hi = lo + c < n ? lo + c : n;
       visit_range(L, lo, hi, f);
     }
