@@ -1003,7 +1003,7 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     }
   }
   S.chunk = bounded_chunk(S.chunk, S.tiled ? S.ntiles : L.n);
-  S.nchunks = chunk_count(L.n, S.chunk > 0 ? S.chunk : 1);
+  if (!S.tiled && S.policy == UPIR_SCHED_STATIC_CHUNK) S.ntiles = chunk_count(L.n, S.chunk);
   int64_t T = sp.num_teams;
   if (S.dist == UPIR_DIST_UNITS) {
     if (T > 1) return upir_fail(c, UPIR_EINVAL, "distribute(units) runs on one team");

@@ -38,11 +38,11 @@ struct LoopK {
 
 struct SchedK {
   int32_t policy, dist;
-  int64_t chunk;    // at most the iterations (tiles) there are
-  int64_t nchunks;  // chunks of the loop (POL_CHUNK, untiled)
+  int64_t chunk;  // at most the iterations (tiles) there are
   int32_t tiled;
   int32_t tile[3];
-  int64_t t0[3], nt[3], ntiles;  // tile grid (tiled only)
+  int64_t t0[3], nt[3];  // tile grid (tiled only)
+  int64_t ntiles;        // its tiles; untiled POL_CHUNK: the loop's chunks
   int32_t T, U;                   // teams, units of the launch
   long long *dyn_next;            // DYNAMIC / GUIDED claim counters (self-resetting), SLOT_WORDS apart
   unsigned *dyn_exit;             // workgroups that finished claiming
@@ -183,7 +183,7 @@ __device__ inline void for_owned_untiled(const LoopK &L, const SchedK &S, int te
     if (tt && unit != 0) return;
     const int64_t first = tu ? (int64_t)team * S.U + unit : (tt ? (int64_t)team : (int64_t)unit);
     const int64_t stride = tu ? (int64_t)S.T * S.U : (tt ? (int64_t)S.T : (int64_t)S.U);
-    for (int64_t m = first; m < S.nchunks; m += stride) {
+    for (int64_t m = first; m < S.ntiles; m += stride) {
       int64_t lo = m * c, hi = lo + c < n ? lo + c : n;
       visit_range(L, lo, hi, f);
     }
