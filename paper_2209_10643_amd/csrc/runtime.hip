@@ -809,6 +809,9 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
       // names, the units; without one that fits, neither does.
       const int32_t units = given ? given->num_units : 0;
       const bool named = fixed && fixed->policy != UPIR_SCHED_AUTO && fixed->tile[0] > 0;
+      // tiles that the caller's schedule deals to a team at a time (split product of 3000^3 on named
+      // 128 x 128 tiles, two at a time: 270 us on 256 units, 295 on 512)
+      const int64_t chunk = named && fixed->policy == UPIR_SCHED_STATIC_CHUNK ? fixed->chunk : 1;
       const int ntiles = is_f32 ? 5 : (units == 512 || named) ? 7 : 6;
       auto suits = [&](const Tile &t) {
         return (!units || t.units == units) && (!named || (t.bm == fixed->tile[0] && t.bn == fixed->tile[1]));
@@ -824,7 +827,16 @@ void default_choice(upir_ctx *c, const upir_loop_obj *lp, upir_spmd &sp, upir_sc
         if (t.pre && t.bm == 256 && t.units == 256 && std::max(M, N) * mm_kpad(K) * 2 >= (1LL << 31)) continue;
         int64_t at_once = (int64_t)t.per * c->num_cus;
         if (given && given->num_teams > 0) at_once = std::min<int64_t>(at_once, given->num_teams);
-        double us = 1e-3 * t.ns * (double)K * (double)cdiv(cdiv(M, t.bm) * cdiv(N, t.bn), at_once);
+        const int64_t ntile = cdiv(M, t.bm) * cdiv(N, t.bn), ch = bounded_chunk(chunk, ntile);
+        double ns = t.ns;
+        if (tiles == bf16 && t.bm == 128 && (named || (given && given->num_teams > 0))) {
+          // a caller's shape may leave a CU to one tile, or the L2s to few: 3000^3 on 64 teams 405 us on
+          // 256 units and 441 on 512, 2000^3 137 and 124
+          const int64_t busy = std::min(at_once, cdiv(ntile, ch));
+          if (t.pre && busy <= c->num_cus) ns = 14.0;
+          if (!t.pre && 2 * busy <= c->num_cus) ns = 15.5;
+        }
+        double us = 1e-3 * ns * (double)K * (double)(cdiv(cdiv(ntile, ch), at_once) * ch);
         if (t.pre) us += 5.0 + (double)(M + N) * (double)K * (is_split ? 8.0 : 6.0) / 5.5e6;
         if (sc.tile[0] == 0 || us < best) {
           best = us;

@@ -69,6 +69,13 @@ def test_matmul_tile_for_few_teams(hctx):
     assert matmul(hctx, "f32", 512, 512, 512)[3] == (32, 32)
 
 
+def test_matmul_units_follow_the_chunk(hctx):
+    # 576 tiles of 128 x 128: two at a time they are one round of two on 256 units (two teams to a CU), two of two on 512
+    tile = (128, 128)
+    assert matmul(hctx, "split", 3000, 3000, 3000, H.make_sched(U.UPIR_SCHED_STATIC_CHUNK, 2, tile=tile))[2] == 256
+    assert matmul(hctx, "split", 3000, 3000, 3000, H.make_sched(U.UPIR_SCHED_STATIC_CHUNK, 2 ** 62, tile=tile))[0] == "matmul_mfma"
+
+
 @pytest.mark.parametrize("kind", ["bf16", "split"])
 def test_matmul_large_tile_on_512_units(hctx, kind):
     for n in (3000, 4096, 8192):
