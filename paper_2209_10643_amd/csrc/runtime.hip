@@ -939,9 +939,6 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
   if (sp.num_teams < 0 || sp.num_units < 0 || sp.num_units > 1024)
     return upir_fail(c, UPIR_EINVAL, "num_teams %d / num_units %d", sp.num_teams, sp.num_units);
   upir_sched sc = lp->sched;
-  upir_spmd dsp;
-  upir_sched dsc;
-  default_choice(c, lp, dsp, dsc, &sp, &sc);
   if (sc.policy == UPIR_SCHED_RUNTIME) {
     upir_sched r{};
     if (!parse_runtime_schedule(r)) return upir_fail(c, UPIR_EINVAL, "UPIR_SCHEDULE is malformed");
@@ -950,7 +947,11 @@ upir_status resolve_plan(upir_ctx *c, const upir_spmd *spmd_in, upir_loop_obj *l
     sc = r;
     upir_status st = validate_sched(c, lp->loop, sc, lp->kind);
     if (st) return st;
-  } else if (sc.policy == UPIR_SCHED_AUTO) {
+  }
+  upir_spmd dsp;
+  upir_sched dsc;
+  default_choice(c, lp, dsp, dsc, &sp, &sc);
+  if (sc.policy == UPIR_SCHED_AUTO) {
     upir_spmd asp = dsp;
     upir_sched asc = dsc;
     auto it = c->tuned.find(lp->key);

@@ -121,6 +121,26 @@ def test_matvec_shape_beside_the_callers(hctx, pol, chunk, n, cols):
         assert shape((0, 0))[1] < 512
 
 
+def test_shape_of_a_schedule_from_the_environment(hctx, monkeypatch):
+    # the shape beside schedule(runtime) is that beside the schedule it stands for
+    S, SC = U.UPIR_SCHED_STATIC, U.UPIR_SCHED_STATIC_CHUNK
+    for text, pol, chunk in ((None, S, 0), ("static", S, 0), ("static,1", SC, 1), ("static,2", SC, 2)):
+        if text is None:
+            monkeypatch.delenv("UPIR_SCHEDULE", raising=False)
+        else:
+            monkeypatch.setenv("UPIR_SCHEDULE", text)
+        for n, cols in ((300, 5000), (8192, 24414), (16384, 16384)):
+            args = U.upir_matvec_args(0x10000000, 0x20000000, 0x30000000, cols, cols)
+            for dist in (U.UPIR_DIST_TEAMS_UNITS, U.UPIR_DIST_UNITS):
+                run, own = (resolve(hctx, U.UPIR_BODY_MATVEC, args, [(0, n, 1)], H.make_sched(p, c, dist))
+                            for p, c in ((U.UPIR_SCHED_RUNTIME, 0), (pol, chunk)))
+                assert run == own, (text, n, cols, dist)
+        for kind in KINDS:
+            run, own = (matmul(hctx, kind, 3000, 3000, 3000, H.make_sched(p, c, tile=(128, 128)))
+                        for p, c in ((U.UPIR_SCHED_RUNTIME, 0), (pol, chunk)))
+            assert run == own, (text, kind)
+
+
 def test_matvec_short_rows_four_to_a_team(hctx):
     shape = lambda n, cols: resolve(hctx, U.UPIR_BODY_MATVEC, U.upir_matvec_args(
         0x10000000, 0x20000000, 0x30000000, cols, cols), [(0, n, 1)])[1:3]
